@@ -158,7 +158,8 @@ hipError_t launch_batch_mark(const BatchArgs& b, hipStream_t s);
 hipError_t launch_batch_close(const BatchArgs& b, uint32_t level, uint32_t width, hipStream_t s);
 hipError_t launch_batch_compact(const BatchArgs& b, hipStream_t s);
 uint32_t batch_compact_chunks(uint32_t n_blocks);
-hipError_t launch_batch_gather(const BatchArgs& b, const DecodeArgs& a, hipStream_t s);
+// max_len: the longest request (0: not known when launched)
+hipError_t launch_batch_gather(const BatchArgs& b, const DecodeArgs& a, uint64_t max_len, hipStream_t s);
 // a one-request descriptor (n = 1, d_out, then lo, hi at output offset 0)
 // written by a kernel from its arguments
 hipError_t launch_put_range(uint64_t* desc, uint64_t d_out, uint64_t lo, uint64_t hi, hipStream_t s);

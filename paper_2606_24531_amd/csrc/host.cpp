@@ -1141,7 +1141,7 @@ static int seek_device(const ace_archive* A, uint64_t lo, uint64_t hi, uint8_t* 
       HIP_TRY(launch_expand_level_dev(a, l, A->all_levels[l + 1] - A->all_levels[l], waves, s));
   }
   if (timed) HIP_TRY(hipEventRecord(T.mat[1], s));
-  HIP_TRY(launch_batch_gather(ba, a, s));
+  HIP_TRY(launch_batch_gather(ba, a, hi - lo, s));
   if (timed) {
     T.n_ent = T.n_mat = 1;
     T.recorded = true;
@@ -1330,7 +1330,7 @@ extern "C" int ace_batch_create(const ace_archive* A, uint32_t cap, void* d_ws, 
       for (uint32_t l = 0; e == hipSuccess && l < A->depth; l++)
         e = launch_expand_level_dev(a, l, A->all_levels[l + 1] - A->all_levels[l], waves, s);
     }
-    if (e == hipSuccess) e = launch_batch_gather(ba, a, s);
+    if (e == hipSuccess) e = launch_batch_gather(ba, a, 0, s);
     hipError_t e2 = hipStreamEndCapture(s, &b->graph);
     if (e != hipSuccess || e2 != hipSuccess) {
       rc = fail(ACE_E_HIP, "graph capture failed: %s", hipGetErrorString(e != hipSuccess ? e : e2));

@@ -894,17 +894,21 @@ __device__ __forceinline__ void store_bytes(uint8_t* p, const uint32_t (&w)[4], 
   if (len & 1) st8(p + o, (uint8_t)x0);
 }
 
-// Copies len bytes of the decoded data from absolute position lo to dst.
-// Each thread takes four 16-byte chunks per step (a blockDim.x * 16 stride
-// apart, so every load and store instruction is coalesced), issues the loads
-// of those whose 16 source bytes lie in one block, then the stores; chunks
-// that cross a block edge or the end go byte by byte.  loc[c] is block c's
-// location.
+// Copies len bytes of the decoded data from absolute position lo to dst, as
+// worker `part` of `parts` workgroups that share the range (steps of
+// 4 * blockDim.x * 16 bytes dealt round robin).  Each thread takes four
+// 16-byte chunks per step (a blockDim.x * 16 stride apart, so every load and
+// store instruction is coalesced) and issues the loads of all four before the
+// stores.  A chunk that crosses a block edge or the range's end reads its
+// bytes one by one, all of them in flight before it writes them: with a byte
+// stored before the next was read, the one such lane of every 16 KiB block of
+// an unaligned range cost 16 memory round trips and set the step's time.
+// loc[c] is block c's location.
 __device__ __forceinline__ void copy_range(const DecodeArgs& a, const uint64_t* loc, uint64_t lo,
-                                           uint64_t len, uint8_t* dst) {
+                                           uint64_t len, uint8_t* dst, uint32_t part, uint32_t parts) {
   constexpr uint32_t kU = 4;
   const uint64_t stride = (uint64_t)blockDim.x * 16;
-  for (uint64_t j0 = threadIdx.x * 16ull; j0 < len; j0 += kU * stride) {
+  for (uint64_t j0 = part * (kU * stride) + threadIdx.x * 16ull; j0 < len; j0 += parts * (kU * stride)) {
     const uint8_t* src[kU];
     bool fast[kU];
 #pragma unroll
@@ -923,17 +927,20 @@ __device__ __forceinline__ void copy_range(const DecodeArgs& a, const uint64_t* 
       if (fast[u]) {
         st16u(dst + j, v[u]);
       } else if (j < len) {
+        const uint32_t n = len - j < 16 ? (uint32_t)(len - j) : 16u;
         uint64_t pos = lo + j, c = blk_of(a, pos), cend = (c + 1) * a.B;
         const uint8_t* base = reinterpret_cast<const uint8_t*>(*gp(loc + c)) - c * a.B;
-        const uint64_t jn = j + 16 < len ? j + 16 : len;
-        for (uint64_t q = j; q < jn; q++, pos++) {
-          if (pos >= cend) {
+        uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (uint32_t q = 0; q < 16; q++, pos++) {
+          if (q < n && pos >= cend) {
             c++;
             cend += a.B;
             base = reinterpret_cast<const uint8_t*>(*gp(loc + c)) - c * a.B;
           }
-          st8(dst + q, ld8(base + pos));
+          if (q < n) w[q >> 2] |= (uint32_t)ld8(base + pos) << (8 * (q & 3));
         }
+        store_bytes(dst + j, w, n);
       }
     }
   }
@@ -1555,7 +1562,7 @@ __global__ __launch_bounds__(kPersistThreads) __attribute__((amdgpu_waves_per_eu
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_copy(DecodeArgs a, const CopyItem* items) {
   const CopyItem it = items[blockIdx.x];
-  copy_range(a, a.loc, it.src_abs, it.len, reinterpret_cast<uint8_t*>(it.dst));
+  copy_range(a, a.loc, it.src_abs, it.len, reinterpret_cast<uint8_t*>(it.dst), 0, 1);
 }
 
 // ---------------------------------------------------------------------------
@@ -1567,13 +1574,16 @@ __global__ __launch_bounds__(256) void k_copy(DecodeArgs a, const CopyItem* item
 // Kept blocks (decoded once, in the first pin_base slots) are never marked:
 // their locations stay valid, and closures stop at them.
 // ---------------------------------------------------------------------------
-__global__ void k_bmark(BatchArgs b) {
+// One wavefront per request (lanes over its target blocks: one thread per
+// request took 120 us for a range of 1,000 blocks, a chain of as many loads).
+__global__ __launch_bounds__(256) void k_bmark(BatchArgs b) {
   const uint64_t n = b.desc[0];
-  for (uint64_t r = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; r < n;
-       r += (uint64_t)gridDim.x * blockDim.x) {
+  const uint32_t lane = threadIdx.x & 63, wpg = blockDim.x >> 6;
+  for (uint64_t r = blockIdx.x * (uint64_t)wpg + (threadIdx.x >> 6); r < n; r += (uint64_t)gridDim.x * wpg) {
     const uint64_t lo = b.desc[2 + 3 * r], hi = b.desc[3 + 3 * r];
     if (hi <= lo || hi > b.n_total) continue;
-    for (uint64_t blk = lo / b.B; blk <= (hi - 1) / b.B; blk++)
+    const uint64_t last = (hi - 1) / b.B;
+    for (uint64_t blk = lo / b.B + lane; blk <= last; blk += 64)
       if (!b.pin[blk]) b.need[blk] = 1;
   }
 }
@@ -1724,7 +1734,11 @@ __global__ __launch_bounds__(kCompactChunk) void k_bwrite(BatchArgs b, uint32_t 
   }
 }
 
-// One workgroup per request: copy [lo, hi) from the decoded slots.
+// gridDim.y workgroups per request (blockIdx.x): copy [lo, hi) from the
+// decoded slots.  Bound by the copy's bytes once a request has a workgroup
+// per 16 KiB: a device-planned seek of 16.4 MB took 4,121 us with one
+// workgroup per request and byte-serial block edges (3,785 us of them here),
+// 284 us now; a graph batch of 1,000 requests of up to 1 MiB 579 -> 364 us.
 __global__ __launch_bounds__(256) void k_bgather(BatchArgs b, DecodeArgs a) {
   const uint64_t n = b.desc[0];
   const uint64_t r = blockIdx.x;
@@ -1732,7 +1746,7 @@ __global__ __launch_bounds__(256) void k_bgather(BatchArgs b, DecodeArgs a) {
   const uint64_t lo = b.desc[2 + 3 * r], hi = b.desc[3 + 3 * r];
   if (hi <= lo || hi > b.n_total) return;
   uint8_t* dst = reinterpret_cast<uint8_t*>(b.desc[1] + b.desc[4 + 3 * r]);
-  copy_range(a, b.loc, lo, hi - lo, dst);
+  copy_range(a, b.loc, lo, hi - lo, dst, blockIdx.y, gridDim.y);
 }
 
 __global__ void k_put_range(uint64_t* desc, uint64_t d_out, uint64_t lo, uint64_t hi) {
@@ -1848,8 +1862,8 @@ hipError_t launch_expand_level_dev(const DecodeArgs& a, uint32_t level, uint32_t
 }
 
 hipError_t launch_batch_mark(const BatchArgs& b, hipStream_t s) {
-  const uint32_t g = (b.cap + 255) / 256;
-  hipLaunchKernelGGL(k_bmark, dim3(g < 1024 ? (g ? g : 1) : 1024), dim3(256), 0, s, b);
+  const uint32_t g = (b.cap + 3) / 4;  // four wavefronts per workgroup, one per request
+  hipLaunchKernelGGL(k_bmark, dim3(g < 2048 ? (g ? g : 1) : 2048), dim3(256), 0, s, b);
   return hipGetLastError();
 }
 
@@ -1876,9 +1890,16 @@ hipError_t launch_put_range(uint64_t* desc, uint64_t d_out, uint64_t lo, uint64_
   return hipGetLastError();
 }
 
-hipError_t launch_batch_gather(const BatchArgs& b, const DecodeArgs& a, hipStream_t s) {
+// Workgroups per request of the gather: one step of copy_range (16 KiB) each
+// when the longest request is known (max_len > 0), else enough that the
+// capacity's requests make kGatherGrid workgroups, of which a short request
+// uses the first few (the others end at once).
+constexpr uint32_t kGatherGrid = 8192, kGatherParts = 1024, kGatherStep = 16384;
+hipError_t launch_batch_gather(const BatchArgs& b, const DecodeArgs& a, uint64_t max_len, hipStream_t s) {
   if (b.cap == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_bgather, dim3(b.cap), dim3(256), 0, s, b, a);
+  uint64_t parts = max_len ? (max_len + kGatherStep - 1) / kGatherStep : kGatherGrid / b.cap;
+  parts = parts < 1 ? 1 : parts > kGatherParts ? kGatherParts : parts;
+  hipLaunchKernelGGL(k_bgather, dim3(b.cap, (uint32_t)parts), dim3(256), 0, s, b, a);
   return hipGetLastError();
 }
 
