@@ -43,9 +43,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ uint8_t ld8(const uint8_t* p) { return *gp(p); }
 __device__ __forceinline__ void st8(uint8_t* p, uint8_t v) { *gp(p) = v; }
 
-__device__ __forceinline__ uint32_t ld16(const uint8_t* p) {
-  return (uint32_t)ld8(p) | ((uint32_t)ld8(p + 1) << 8);
-}
 __device__ __forceinline__ uint32_t ld32(const uint8_t* p) {
   return *gp(reinterpret_cast<const uint32_t*>(p));  // callers pass 4-aligned addresses
 }
@@ -109,26 +106,50 @@ __device__ __forceinline__ uint64_t blk_of(const DecodeArgs& a, uint64_t x) {
 // Entropy layer: a group of G lanes (G = 64, or 32 when W <= 32, so that one
 // wavefront decodes two streams side by side) decodes one rANS stream.
 //
-// LDS holds each stream's 12-bit table as a 4096-byte slot -> symbol map plus
-// one packed word per symbol (f << 16 | cum), and a ring of two chunks of
-// renormalisation words (8 G bytes each), refilled from a register
-// prefetch so the decode loop never waits on HBM latency.  The table build's
-// scratch lives in the ring before the ring is filled.  Lane j of a group
-// owns state j; each step decodes symbols t*W .. t*W+W-1, and the lanes that
-// renormalise take consecutive words in lane order: word = running position
-// + (count of renormalising lanes below in the group).  The loop body is
+// LDS holds each stream's 12-bit table and a ring of two chunks of
+// renormalisation words (8 G bytes each), refilled from a register prefetch so
+// the decode loop never waits on HBM latency.  The table is one of two:
+//   * narrow: a 4096-byte slot -> symbol map plus one packed word per symbol
+//     (f << 16 | cum): 6 KiB per stream, so a CU holds 26 streams, and a step
+//     is three dependent LDS reads (symbol, word, renormalisation word);
+//   * wide (kWide, G = 64): one word per slot (symbol | slot - cum << 8 |
+//     f - 1 << 20): 17.5 KiB per stream, nine streams per CU, and a step is
+//     two dependent LDS reads.
+// A launch whose streams fit on the device with wide tables lasts as long as
+// its longest stream, a chain of steps, and a shorter step is what helps; in a
+// larger one the streams in flight hide each other's latency.
+// Lane j of a group owns state j; each step decodes symbols t*W .. t*W+W-1,
+// and the lanes that renormalise take consecutive words in lane order: word =
+// running position + (count of renormalising lanes below in the group).  The
+// ring's first G words are repeated after its end, so that only the running
+// position wraps and a lane's count is added to it as it is.  The loop body is
 // branch-free apart from the ring refill, and each step's symbols are stored
 // straight to the output (one coalesced store per step, no LDS staging).
+//
+// A stream's first KiB (all of its table and states) is staged in LDS by one
+// round of loads, and the first ring chunks are requested as soon as the
+// table's size is known, before it is built: the loads before the first step
+// are three dependent round trips (plan entry, descriptor, stream), where
+// reading each field as it was needed took about fifteen.
 // ---------------------------------------------------------------------------
-template <uint32_t G>
+typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
+
+template <uint32_t G, bool kWide>
 struct RansGroup {
-  uint8_t sym[4096];  // slot -> symbol
-  uint32_t fc[256];   // symbol -> f << 16 | cum
+  static_assert(!kWide || G == 64, "wide tables: one stream per wavefront");
+  static constexpr uint32_t kHead = 1024;  // bytes staged: table (at most 544) and states (256)
   union {
-    u32x2 ring[2 * G];  // 2 chunks x G lanes x 8 B
+    u32x4 head[kHead / 16];             // the stream's first bytes, until the table is built
+    uint8_t sym[4096];                  // narrow: slot -> symbol
+    uint32_t tab[kWide ? 4096 : 1024];  // wide: slot -> symbol | (slot - cum) << 8 | (f - 1) << 20
+  } t;
+  uint32_t fc[kWide ? 1 : 256];  // narrow: symbol -> f << 16 | cum
+  union {
+    u32x2 ring[2 * G + G / 4];  // 2 chunks x G lanes x 8 B, then the first G words again
     struct {
-      unsigned long long starts[64];  // bit t set: a symbol's interval starts at slot t
-      uint8_t by_rank[4 + 256 + 8];   // k-th present symbol at byte k + 4 (read 8 bytes at a time)
+      unsigned long long starts[64];  // narrow: bit t, wide: bit t - 1 set: a symbol's interval starts at slot t
+      uint8_t by_rank[kWide ? 4 : 4 + 256 + 8];  // narrow: k-th present symbol at byte k + 4 (read 8 bytes at a time)
+      uint32_t rank[kWide ? 256 : 1];            // wide: k-th present symbol's entry, less the slot
     } b;
   } u;
 };
@@ -156,18 +177,30 @@ __device__ __forceinline__ bool grp_any(bool v, uint32_t h) {
 // Decodes one stream per group; `on` (group-uniform) says whether the group
 // has a stream.  Every lane of the wave must call it.  Returns true (for the
 // group's lanes) when the group's stream breaks a format rule.
-template <uint32_t G>
+template <uint32_t G, bool kWide>
 __device__ __forceinline__ bool rans_decode_group(const uint8_t* src, uint32_t clen, uint32_t n, uint32_t W,
-                                                  uint8_t* dst, RansGroup<G>& sm, uint32_t g, uint32_t h,
+                                                  uint8_t* dst, RansGroup<G, kWide>& sm, uint32_t g, uint32_t h,
                                                   bool on) {
   constexpr uint32_t kSpl = 256 / G;      // symbols per lane in the table build
   constexpr uint32_t kChunkW = 4 * G;     // words per ring chunk (at least the kU * W of one check)
-  // ---- frequency table: 32-byte presence bitmap, then f-1 per present symbol
+  // ---- the stream's head (readable past the stream's end: the archive's slack)
   bool bad = on && clen < 32;
   on = on && !bad;
-  const uint32_t bits = !on ? 0u
-                        : G == 64 ? ((uint32_t)src[g >> 1] >> ((g & 1) * 4)) & 0xFu
-                                  : (uint32_t)src[g];
+  constexpr uint32_t kHq = RansGroup<G, kWide>::kHead / (16 * G);
+  if (on) {
+    u32x4 hd[kHq];
+#pragma unroll
+    for (uint32_t q = 0; q < kHq; q++)
+      hd[q] = *reinterpret_cast<const ACE_GLOBAL u32x4_a4*>(gp(src + 16 * (g + q * G)));
+#pragma unroll
+    for (uint32_t q = 0; q < kHq; q++) sm.t.head[g + q * G] = hd[q];
+  }
+  wave_sync();
+  const uint8_t* hb = reinterpret_cast<const uint8_t*>(sm.t.head);
+  const uint16_t* hb16 = reinterpret_cast<const uint16_t*>(sm.t.head);
+  const uint32_t* hb32 = reinterpret_cast<const uint32_t*>(sm.t.head);
+  // ---- frequency table: 32-byte presence bitmap, then f-1 per present symbol
+  const uint32_t bits = !on ? 0u : G == 64 ? ((uint32_t)hb[g >> 1] >> ((g & 1) * 4)) & 0xFu : (uint32_t)hb[g];
   const uint32_t cnt = __popc(bits);
   const uint32_t cnt_in = grp_incl_sum<G>(cnt);
   const uint32_t before = cnt_in - cnt;
@@ -175,16 +208,42 @@ __device__ __forceinline__ bool rans_decode_group(const uint8_t* src, uint32_t c
   const uint32_t tsz = (32 + 2 * present + 3) & ~3u;
   if (on && (present == 0 || tsz + 4 * W > clen || ((clen - tsz - 4 * W) & 1))) bad = true;
   on = on && !bad;
+  // ---- the first ring chunks, on their way while the table is built
+  const uint8_t* wsrc = src + tsz + 4 * W;
+  const uint32_t nwords = on ? (clen - tsz - 4 * W) >> 1 : 0;
+  const uintptr_t a0 = (uintptr_t)wsrc & ~(uintptr_t)7;
+  uint32_t hw = (uint32_t)((uintptr_t)wsrc - a0) >> 1;  // word 0 in chunk 0
+  uint32_t nchunks = on ? (2 * (hw + nwords) + 8 * G - 1) / (8 * G) : 0;
+  if (G == 64) {
+    hw = uniform(hw);
+    nchunks = uniform(nchunks);
+  }
+  const ACE_GLOBAL u32x2* gch = gp(reinterpret_cast<const u32x2*>(a0));
+  u32x2 r0, r1, pf;
+  r0.x = r0.y = r1.x = r1.y = pf.x = pf.y = 0;
+  if (nchunks) {  // chunks past the last are not used
+    r0 = gch[g];
+    r1 = gch[min(1u, nchunks - 1) * G + g];
+    pf = gch[min(2u, nchunks - 1) * G + g];
+  }
+  uint32_t committed = min(2u, nchunks);
+  // ---- frequencies and states, from the staged head
   uint32_t f[kSpl], mysum = 0, k = before;
 #pragma unroll
   for (uint32_t j = 0; j < kSpl; j++) {
-    f[j] = (on && ((bits >> j) & 1)) ? ld16(src + 32 + 2 * (k++)) + 1 : 0;
+    f[j] = (on && ((bits >> j) & 1)) ? (uint32_t)hb16[16 + k++] + 1 : 0;
     mysum += f[j];
   }
+  // W <= 32 of 64 lanes: lane g repeats what lane g mod W does, so that every
+  // lane has a symbol and a place to store it (the same byte, from each)
+  const bool rep = G == 64 && W <= 32;
+  const uint32_t lane_w = rep ? g % W : g;
+  uint32_t x = (on && lane_w < W) ? hb32[(tsz >> 2) + lane_w] : kL;
   const uint32_t sum_in = grp_incl_sum<G>(mysum);
   uint32_t cum = sum_in - mysum;
   const uint32_t total = grp_last<G>(sum_in, h);
-  if (on && total != kM) bad = true;
+  if (on && (total != kM || (g < W && x < kL))) bad = true;
+  bad = grp_any<G>(bad, h);
   on = on && !bad;
   for (uint32_t j = g; j < 64; j += G) sm.u.b.starts[j] = 0ull;
   wave_sync();
@@ -193,31 +252,60 @@ __device__ __forceinline__ bool rans_decode_group(const uint8_t* src, uint32_t c
 #pragma unroll
     for (uint32_t j = 0; j < kSpl; j++) {
       const uint32_t s = kSpl * g + j;
-      sm.fc[s] = f[j] ? (f[j] << 16) | cum : 0u;
-      if (f[j]) {
-        sm.u.b.by_rank[4 + k++] = (uint8_t)s;
-        atomicOr(&sm.u.b.starts[cum >> 6], 1ull << (cum & 63));
+      if (kWide) {
+        if (f[j]) {
+          sm.u.b.rank[k++ & (kWide ? 255u : 0u)] = ((f[j] - 1) << 20) - (cum << 8) + s;
+          if (cum) atomicOr(&sm.u.b.starts[(cum - 1) >> 6], 1ull << ((cum - 1) & 63));
+        }
+      } else {
+        sm.fc[kWide ? 0 : s] = f[j] ? (f[j] << 16) | cum : 0u;
+        if (f[j]) {
+          sm.u.b.by_rank[4 + k++] = (uint8_t)s;
+          atomicOr(&sm.u.b.starts[cum >> 6], 1ull << (cum & 63));
+        }
       }
       cum += f[j];
     }
   }
   wave_sync();
-  // ---- slot -> symbol: lane g fills slots 4096/G * g onwards, four slots
-  // (one word) at a time.  The symbol of slot t has rank (interval starts at
-  // or before t) - 1, so a word's four symbols have ranks prev + c_b, where
-  // prev is the rank just before the word and c_b counts the word's starts
-  // up to slot b (0..4).  The word is then one byte permute of the 8 rank
-  // bytes from prev on: c_b for all four b at once is the word's 4 start
-  // bits spread one per byte (a multiply) and prefix-summed across the bytes
-  // (a multiply by 0x01010101).  Ranks are stored 4 bytes in, so prev = -1
-  // (lane 0; slot 0 always starts an interval) stays in bounds.
-  {
+  if (kWide) {
+    // ---- slot -> entry: lane g fills slots 64 j + g (consecutive words per
+    // step, no bank conflicts).  Slot 0 always starts an interval, so the
+    // rank of slot t's symbol is the count of starts at slots 1 .. t: the
+    // bits below t of the shifted bitmap, that is the words before word j
+    // and, in it, the bits below the lane (mbcnt).  An entry is its rank's
+    // word, whose slot field holds -cum, plus the slot.
+    const unsigned long long w = sm.u.b.starts[g & 63];
+    const uint32_t wlo = (uint32_t)w, whi = (uint32_t)(w >> 32);
+    if (on) {
+      uint32_t pre = 0, t8 = g << 8;
+#pragma unroll 8
+      for (uint32_t j = 0; j < 64; j++) {
+        const uint32_t slo = (uint32_t)__builtin_amdgcn_readlane((int)wlo, j);
+        const uint32_t shi = (uint32_t)__builtin_amdgcn_readlane((int)whi, j);
+        const uint32_t r = __builtin_amdgcn_mbcnt_hi(shi, __builtin_amdgcn_mbcnt_lo(slo, 0u));
+        // every start has a symbol, so a rank is below the symbols present
+        sm.t.tab[(64 * j + g) % (kWide ? 4096 : 1024)] = sm.u.b.rank[(pre + r) & (kWide ? 255u : 0u)] + t8;
+        pre += __popc(slo) + __popc(shi);
+        t8 += 64u << 8;
+      }
+    }
+  } else {
+    // ---- slot -> symbol: lane g fills slots 4096/G * g onwards, four slots
+    // (one word) at a time.  The symbol of slot t has rank (interval starts at
+    // or before t) - 1, so a word's four symbols have ranks prev + c_b, where
+    // prev is the rank just before the word and c_b counts the word's starts
+    // up to slot b (0..4).  The word is then one byte permute of the 8 rank
+    // bytes from prev on: c_b for all four b at once is the word's 4 start
+    // bits spread one per byte (a multiply) and prefix-summed across the bytes
+    // (a multiply by 0x01010101).  Ranks are stored 4 bytes in, so prev = -1
+    // (lane 0; slot 0 always starts an interval) stays in bounds.
     constexpr uint32_t kWpl = 64 / G;  // 64-bit start words per lane
     uint32_t pc = 0;
 #pragma unroll
     for (uint32_t q = 0; q < kWpl; q++) pc += __popcll(sm.u.b.starts[kWpl * g + q]);
     uint32_t prev = grp_incl_sum<G>(pc) - pc + 3;  // rank before the lane's first slot, + 4
-    uint32_t* out32 = reinterpret_cast<uint32_t*>(sm.sym) + 16 * kWpl * g;
+    uint32_t* out32 = reinterpret_cast<uint32_t*>(sm.t.sym) + 16 * kWpl * g;
     const uint32_t* br32 = reinterpret_cast<const uint32_t*>(sm.u.b.by_rank);
     if (on) {
 #pragma unroll
@@ -235,66 +323,81 @@ __device__ __forceinline__ bool rans_decode_group(const uint8_t* src, uint32_t c
     }
   }
   wave_sync();  // the build scratch is dead from here: the ring reuses it
-  // ---- states and word ring
-  const uint8_t* wsrc = src + tsz + 4 * W;
-  const uint32_t nwords = on ? (clen - tsz - 4 * W) >> 1 : 0;
-  uint32_t x = (on && g < W) ? ld32(src + tsz + 4 * g) : kL;
-  if (on && g < W && x < kL) bad = true;
-  bad = grp_any<G>(bad, h);
-  on = on && !bad;
-  const uintptr_t a0 = (uintptr_t)wsrc & ~(uintptr_t)7;
-  const uint32_t hw = (uint32_t)((uintptr_t)wsrc - a0) >> 1;  // word 0 in chunk 0
-  const uint32_t nchunks = on ? (2 * (hw + nwords) + 8 * G - 1) / (8 * G) : 0;
-  const ACE_GLOBAL u32x2* gch = gp(reinterpret_cast<const u32x2*>(a0));
-  uint32_t committed = 0;
-  for (; committed < 2 && committed < nchunks; committed++)
-    sm.u.ring[(committed & 1) * G + g] = gch[committed * G + g];
-  u32x2 pf;
-  pf.x = 0;
-  pf.y = 0;
-  if (committed < nchunks) pf = gch[committed * G + g];
+  if (nchunks) {
+    sm.u.ring[g] = r0;
+    if (g < G / 4) sm.u.ring[2 * G + g] = r0;
+    sm.u.ring[G + g] = r1;
+  }
+  // the prefetch is waited for here: the loop's refills then know that at
+  // least one check's stores were issued after the load they wait for, and
+  // wait for that load alone instead of for every store in flight
+  uint32_t pf0 = pf.x, pf1 = pf.y;
+  ACE_OPAQUE(pf0);
+  ACE_OPAQUE(pf1);
   wave_sync();
   const uint16_t* ring16 = reinterpret_cast<const uint16_t*>(sm.u.ring);
   uint32_t rp = hw;  // ring position (in words) of the next unread word
-  const bool lane_on = on && g < W;
   const uint32_t my_steps = on ? (n + W - 1) / W : 0;
   const uint32_t nsteps = uniform(G == 64 ? my_steps : max(my_steps, (uint32_t)__shfl_xor(my_steps, 32, 64)));
   // Each step's decoded symbols go straight to their output bytes: lane j
   // writes byte t*W + j, so a step is one coalesced W-byte store.
   constexpr uint32_t kU = 4;  // steps per ring check in the main loop
-  uint8_t* op = dst + g;      // this lane's next output byte
+  uint8_t* op = dst + lane_w;  // this lane's next output byte
+  const uint32_t half = h ? 0u : ~0u;  // G = 32: the first half's ballot counts below its own lanes only
+  const uint32_t rep_below = (1u << (lane_w & 31)) - 1u;  // W <= 32 of 64 lanes: the states below this one
   // Makes room for `steps` more steps in the word ring.
   auto prepare = [&](uint32_t steps) {
     const bool refill = rp + steps * W > committed * kChunkW && committed < nchunks;  // group-uniform
     if (__ballot(refill)) {
       if (refill) {
-        sm.u.ring[(committed & 1) * G + g] = pf;
+        u32x2 v;
+        v.x = pf0;
+        v.y = pf1;
+        sm.u.ring[(committed & 1) * G + g] = v;
+        if (!(committed & 1) && g < G / 4) sm.u.ring[2 * G + g] = v;
         committed++;
-        if (committed < nchunks) pf = gch[committed * G + g];
+        const u32x2 q = gch[min(committed, nchunks - 1) * G + g];
+        pf0 = q.x;
+        pf1 = q.y;
       }
       wave_sync();
     }
   };
-  // One step.  kAll: every lane of the wave holds a state with a symbol in
-  // this step, so the renormalisation ballot is the comparison itself.
-  auto step = [&](auto all, bool act) {
-    constexpr bool kAll = decltype(all)::value;
-    const uint32_t slot = x & (kM - 1);
-    const uint32_t s = sm.sym[slot];
-    const uint32_t e = sm.fc[s];
-    const uint32_t xn = __umul24(e >> 16, x >> kProbBits) + (slot - (e & 0xFFFFu));  // low half: cum
+  // One step.  kind 3: every lane holds or repeats a state with a symbol in
+  // this step (all_m: the lanes that hold one); 2: every lane holds one; 1:
+  // every lane below W does (all_m: those lanes), the others compute along on
+  // states of their own, store nothing and are not counted; 0: the lanes with
+  // act set.  (A store under a condition may be skipped, so that the refill
+  // cannot tell how many stores followed its load and waits for all of them:
+  // kinds 2 and 3 store from every lane.)
+  auto step = [&](auto kind, bool act, uint64_t all_m) {
+    constexpr int kKind = decltype(kind)::value;
+    constexpr bool kFull = kKind >= 2, kAll = kKind >= 1;
+    const uint32_t slot = x & (kM - 1), xh = x >> kProbBits;
+    uint32_t s, xn;
+    if (kWide) {
+      s = sm.t.tab[slot % (kWide ? 4096 : 1024)];  // the symbol is the low byte
+      xn = __umul24(s >> 20, xh) + (xh + ((s >> 8) & 0xFFFu));
+    } else {
+      s = sm.t.sym[slot];
+      ACE_OPAQUE(s);
+      const uint32_t e = sm.fc[kWide ? 0 : s & 255u];
+      xn = __umul24(e >> 16, xh) + (slot - (e & 0xFFFFu));  // low half: cum
+    }
     const bool lt = xn < kL;
-    const bool need = kAll ? lt : (act && lt);
-    const uint64_t m = __builtin_amdgcn_ballot_w64(need);
+    uint64_t m = __builtin_amdgcn_ballot_w64(kAll ? lt : (act && lt));
+    if (kAll && kKind != 2) m &= all_m;
     const uint32_t mlo = (uint32_t)m, mhi = (uint32_t)(m >> 32);
-    const uint32_t pos = __builtin_amdgcn_mbcnt_hi(mhi, __builtin_amdgcn_mbcnt_lo(G == 64 || h == 0 ? mlo : 0u, rp));
-    uint32_t wd = ring16[(pos & (2 * kChunkW - 1))];
+    const uint32_t below =
+        kKind == 3 ? (uint32_t)__popc(mlo & rep_below)
+                   : __builtin_amdgcn_mbcnt_hi(mhi, __builtin_amdgcn_mbcnt_lo(G == 64 ? mlo : mlo & half, 0u));
+    uint32_t wd = ring16[(rp & (2 * kChunkW - 1)) + below];
     ACE_OPAQUE(wd);  // read for every lane: keeps the update branch-free
-    const uint32_t xa = (kAll || act) ? xn : x;
-    x = need ? ((xn << 16) | wd) : xa;
+    const uint32_t xr = lt ? ((xn << 16) | wd) : xn;
+    x = (kAll || act) ? xr : x;
     rp += (uint32_t)(G == 64 ? __popcll(m) : __popc(h ? mhi : mlo));
-    if (kAll || act) st8(op, (uint8_t)s);
-    op += kAll ? G : W;  // kAll: W == G
+    if (kFull || (kAll ? g < W : act)) st8(op, (uint8_t)s);
+    op += kKind == 2 ? G : W;
   };
   // main loop: steps where every state of both groups has a symbol, kU at a
   // time with one check; then the ragged tail one step at a time
@@ -302,22 +405,31 @@ __device__ __forceinline__ bool rans_decode_group(const uint8_t* src, uint32_t c
   const uint32_t t_full =
       uniform(G == 64 ? my_full : min(my_full, (uint32_t)__shfl_xor(my_full, 32, 64))) & ~(kU - 1);
   uint32_t t = 0;
-  if (W == G) {  // every lane holds a state: no per-lane activity in the main loop
+  const uint64_t lanes = __ballot(g < W);
+  if (rep) {
     for (; t < t_full; t += kU) {
       prepare(kU);
 #pragma unroll
-      for (uint32_t u = 0; u < kU; u++) step(std::true_type{}, true);
+      for (uint32_t u = 0; u < kU; u++) step(std::integral_constant<int, 3>{}, true, lanes);
+    }
+  } else if (W == G) {
+    for (; t < t_full; t += kU) {
+      prepare(kU);
+#pragma unroll
+      for (uint32_t u = 0; u < kU; u++) {
+        step(std::integral_constant<int, 2>{}, true, ~0ull);
+      }
     }
   } else {
     for (; t < t_full; t += kU) {
       prepare(kU);
 #pragma unroll
-      for (uint32_t u = 0; u < kU; u++) step(std::false_type{}, lane_on);
+      for (uint32_t u = 0; u < kU; u++) step(std::integral_constant<int, 1>{}, true, lanes);
     }
   }
   for (; t < nsteps; t++) {
     prepare(1);
-    step(std::false_type{}, lane_on && g + t * W < n);
+    step(std::integral_constant<int, 0>{}, on && g < W && g + t * W < n, 0);
   }
   if (on && (rp - hw != nwords || (g < W && x != kL))) bad = true;
   return grp_any<G>(bad, h);
@@ -460,9 +572,9 @@ __global__ __launch_bounds__(64) void k_rans_enc(EncArgs e) {
 // left in place (the expansion reads them there).  Also records where each
 // block's bytes will live.
 // Stream t of plan entry i (on: the group has an entry), one group of G lanes.
-template <uint32_t G>
+template <uint32_t G, bool kWide>
 __device__ __forceinline__ void rans_entry(const DecodeArgs& a, uint32_t i, bool on, uint32_t t,
-                                           RansGroup<G>& sm, uint32_t g, uint32_t h) {
+                                           RansGroup<G, kWide>& sm, uint32_t g, uint32_t h) {
   // only the fields this kernel needs (no whole-entry copy: raw[t] is
   // indexed by the grid's y coordinate)
   const PlanEntry* pp = a.plan + (on ? i : 0);
@@ -481,16 +593,17 @@ __device__ __forceinline__ void rans_entry(const DecodeArgs& a, uint32_t i, bool
   const uint8_t* d = a.arch + pay + kSDesc * t;
   uint32_t n = 0, clen = 0, off = 0;
   if (on) {
-    n = ld32(d + 4);
-    clen = ld32(d + 8);
-    off = ld32(d + 12);
+    const u32x4 v = *gp(reinterpret_cast<const u32x4*>(d));  // payloads are 16-aligned
+    n = v.y;
+    clen = v.z;
+    off = v.w;
   }
   uint8_t* dst = t == 0 ? a.lit + (uint64_t)i * a.B
                : t == 1 ? a.lens + 4ull * seq_base
                         : a.offs + (uint64_t)a.ow * seq_base;
   const uint8_t* src = a.arch + pay + off;
   const unsigned long long c0 = a.trace ? (unsigned long long)wall_clock64() : 0ull;
-  if (rans_decode_group<G>(src, clen, n, a.W, dst, sm, g, h, on) && g == 0) flag(a.err, kErrCorrupt);
+  if (rans_decode_group<G, kWide>(src, clen, n, a.W, dst, sm, g, h, on) && g == 0) flag(a.err, kErrCorrupt);
   if (a.trace && on && g == 0) {
     a.trace[8ull * i + 2 + 2 * t] = c0;
     a.trace[8ull * i + 3 + 2 * t] = (unsigned long long)wall_clock64();
@@ -504,10 +617,10 @@ __device__ __forceinline__ void rans_entry(const DecodeArgs& a, uint32_t i, bool
 // LEN to lens + 4 * seq_base and OFF to offs + ow * seq_base; raw streams
 // are left in place (the expansion reads them there).  Also records where
 // each block's bytes will live.
-template <uint32_t G>
+template <uint32_t G, bool kWide>
 __global__ __launch_bounds__(64) void k_rans(DecodeArgs a, uint32_t plan_lo, uint32_t plan_hi, int lv_lo,
                                              int lv_hi) {
-  __shared__ RansGroup<G> sm[64 / G];
+  __shared__ RansGroup<G, kWide> sm[64 / G];
   const uint32_t lane = threadIdx.x, h = lane / G, g = lane % G, t = blockIdx.y;
   if (lv_lo >= 0) {  // the plan range of levels [lv_lo, lv_hi), from device memory
     plan_lo = a.lvl_dev[lv_lo];
@@ -519,7 +632,7 @@ __global__ __launch_bounds__(64) void k_rans(DecodeArgs a, uint32_t plan_lo, uin
     const uint32_t i = plan_lo + bx * (64 / G) + h;
     const bool on = i < plan_hi;
     if (!__ballot(on)) return;
-    rans_entry<G>(a, i, on, t, sm[h], g, h);
+    rans_entry<G, kWide>(a, i, on, t, sm[h], g, h);
   }
 }
 
@@ -1765,6 +1878,14 @@ __global__ void k_fill_u32(uint32_t* p, uint32_t v, uint64_t n) {
 // Grid caps of launches whose plan length is read on the device.
 constexpr uint32_t kStrideGridRans = 4096, kStrideGridExpand = 2048;
 
+// Entropy launches of at most this many blocks take wide tables: nine streams
+// per CU on 256 CUs, so the literal streams (the long ones, dispatched first)
+// are all in flight at once.  Measured, wide against narrow: 768 blocks of
+// 64 KiB 103 / 121 us, 988 of 10,000 bytes 40 / 48 us, 2,048 of 16 KiB (W = 32)
+// 63 / 78 us; 16,384 blocks 173 / 87 us (the wide tables leave two wavefronts
+// per SIMD).  Two streams per wavefront asked for by the caller stay narrow.
+constexpr uint32_t kWideBlocks = 2304;
+
 // Entropy launch over plan entries [lo, hi), or (lv_lo >= 0) over the plan
 // range of levels [lv_lo, lv_hi) read from device memory, with hi - lo
 // entries of capacity.
@@ -1772,7 +1893,8 @@ static hipError_t launch_rans_any(const DecodeArgs& a, uint32_t lo, uint32_t hi,
                                   uint32_t per_wave, hipStream_t s) {
   if (hi <= lo) return hipSuccess;
   const uint32_t n = hi - lo;
-  if (per_wave == 0) per_wave = a.W <= 32 ? 2 : 1;
+  const bool wide = per_wave != 2 && n <= kWideBlocks;
+  if (per_wave == 0) per_wave = a.W <= 32 && !wide ? 2 : 1;
   const bool two = per_wave == 2 && a.W <= 32;
   uint32_t grid = two ? (n + 1) / 2 : n;
   // a plan whose length is read on the device is covered by striding over a
@@ -1780,9 +1902,11 @@ static hipError_t launch_rans_any(const DecodeArgs& a, uint32_t lo, uint32_t hi,
   const bool dev = lv_lo >= 0 || a.n_plan_dev;
   if (dev && grid > kStrideGridRans) grid = kStrideGridRans;
   if (two)
-    hipLaunchKernelGGL(k_rans<32>, dim3(grid, 3), dim3(64), 0, s, a, lo, hi, lv_lo, lv_hi);
+    hipLaunchKernelGGL((k_rans<32, false>), dim3(grid, 3), dim3(64), 0, s, a, lo, hi, lv_lo, lv_hi);
+  else if (wide)
+    hipLaunchKernelGGL((k_rans<64, true>), dim3(grid, 3), dim3(64), 0, s, a, lo, hi, lv_lo, lv_hi);
   else
-    hipLaunchKernelGGL(k_rans<64>, dim3(grid, 3), dim3(64), 0, s, a, lo, hi, lv_lo, lv_hi);
+    hipLaunchKernelGGL((k_rans<64, false>), dim3(grid, 3), dim3(64), 0, s, a, lo, hi, lv_lo, lv_hi);
   return hipGetLastError();
 }
 
