@@ -675,20 +675,36 @@ constexpr uint32_t kUnres = kPoison | kSlow | kPend;  // flags of a span without
 constexpr uint32_t kDepCache = 800;  // dependency lists cached in LDS per block (longer: read from HBM)
 constexpr uint32_t kMaxJumps = 12;   // pointer-doubling rounds (chains up to 4096)
 constexpr uint32_t kPer = 2;         // output pieces per thread per round
+constexpr uint32_t kSlowPer = 8;     // slow bytes per thread per round
+// A tile with more slow bytes per thread than this resolves them in rounds
+// (slow_rounds), one with fewer follows each run back by itself.  A round costs
+// about 7 us however few bytes it holds; walking costs 2 us a tile when there
+// are few and, in the genome blocks that copy regions just written, whose
+// chains are up to ten hops long, 50 (16 KiB) to 150 us (64 KiB), which set
+// the end of their level.  Expansion of 256 MiB mixed at 1, 2 and 4: 354, 354
+// and 354 us (415 without rounds); of 48 MiB in 64 KiB blocks 217, 203 and 203
+// us (302); of 9.9 MB of text in 10,000-byte blocks 91, 94 and 100 us (102).
+constexpr uint32_t kSlowWalk = 2;
 
 template <uint32_t kThreads>
 struct ExpandSmem {
   static constexpr uint32_t kSeq = 2 * kThreads;    // sequences per tile (two per thread)
   static constexpr uint32_t kRound = kPer * kThreads;  // output pieces per round (kPer per thread)
-  uint32_t cseq[kRound];  // marks: the sequence whose first piece is each piece of the round (0 = none)
-  uint32_t pfx[kSeq];     // index of the sequence's first output piece in the tile
+  static constexpr uint32_t kSlowRound = kSlowPer * kThreads;  // slow bytes resolved at a time
+  union {
+    struct {
+      uint32_t cseq[kRound];  // marks: the sequence whose first piece is each piece of the round (0 = none)
+      uint32_t pfx[kSeq];     // index of the sequence's first output piece in the tile
+      uint64_t src0[kSeq];    // address of the first byte of a resolved span
+    };
+    uint32_t par[kSlowRound];  // after the pieces: where each slow byte of a round comes from
+  };
   uint32_t dst[kSeq];     // block-relative start of the sequence
   uint32_t lm[kSeq];      // L | M << 16
   uint32_t lit[kSeq];     // index of the sequence's first literal in the literal stream
   uint32_t dfl[kSeq];     // min(d, 2^24 - 1) | flags << 24
   uint32_t win[kSeq];     // readable bytes around src0: back (0..31) | forward << 5; unresolved: O - block start
   uint32_t ptr[kSeq];     // pending span: span of sequence (ptr >> 16) from offset (ptr & 0xFFFF)
-  uint64_t src0[kSeq];    // address of the first byte of a resolved span
   uint32_t deps[kDepCache];
   uint32_t scan[kPer * kThreads / 64 > 32 ? kPer * kThreads / 64 : 32];
 };
@@ -944,6 +960,161 @@ __device__ __forceinline__ uint32_t slow_slot(const ExpandSmem<kThreads>& sm, co
   return lo;
 }
 
+// A slow byte's entry while a round of them is resolved: another slow byte of
+// the round (kFromSlow | its index), a byte of this block's output (its
+// position, with kFromExt when that byte came from an earlier block), or a
+// byte of an earlier block (kFromBlock | the number of the slow byte that
+// copies it).
+constexpr uint32_t kFromSlow = 1u << 31, kFromBlock = 1u << 30, kFromExt = 1u << 29, kFromMask = (1u << 29) - 1;
+
+// The source of slow byte u of the tile, in slot k, as a position relative to
+// the block's start in r; false: in an earlier block, too far back for that.
+template <uint32_t kThreads>
+__device__ __forceinline__ bool slow_source(const ExpandSmem<kThreads>& sm, uint32_t k, uint32_t u, uint32_t& im,
+                                            int32_t& r) {
+  const uint32_t Mk = sm.lm[k] >> 16, i = u - (sm.ptr[k] - Mk), d = sm.dfl[k] & 0xFFFFFFu;
+  im = i < d ? i : i - d * udiv_small(i, d);  // i < 2^16
+  const uint32_t orel = sm.win[k];
+  r = (int32_t)(orel + im);
+  return orel != kOrelFar;
+}
+
+// Address of the byte of an earlier block that slow byte u copies (null when
+// earlier blocks may not be read).
+template <uint32_t kThreads>
+__device__ __forceinline__ const uint8_t* slow_ext_addr(const DecodeArgs& a, const ExpandSmem<kThreads>& sm,
+                                                        const BlockCtx& c, uint32_t u) {
+  if (!c.ext_ok) return nullptr;
+  const uint32_t k = slow_slot<kThreads>(sm, c, u);
+  uint32_t im;
+  int32_t r;
+  uint64_t src;
+  if (slow_source<kThreads>(sm, k, u, im, r)) {
+    src = c.bs + (uint64_t)(int64_t)r;
+  } else {
+    const uint32_t q = c.t0 + k;
+    src = (c.ow == 4 ? (uint64_t)ld32(c.offs + 4ull * q) : ld64(c.offs + 8ull * q)) + im;
+  }
+  const uint64_t blk = blk_of(a, src);
+  return reinterpret_cast<const uint8_t*>(blk_loc(a, blk)) + (src - blk * a.B);
+}
+
+// The tile's n_slow slow bytes, kSlowPer per thread at a time.  Each byte
+// first finds what it copies: a byte of the output that the pieces (or an
+// earlier round) write, a byte of an earlier block, or another slow byte of
+// the round, always an earlier one.  Those chains are followed in LDS, one
+// hop per step for all of a thread's bytes, each step leaving what it found
+// for the bytes behind it, so a chain of n takes about log2(n) steps.  Then
+// every byte is read from the output (after a barrier that waits for the
+// stores before it) and written, all of a thread's loads in flight at once.
+// Returns the bytes that came from earlier blocks.  The LDS dependency list
+// is overwritten when there is more than one round (it then holds one bit per
+// slow byte: from an earlier block).  Every thread must call it.
+template <uint32_t kThreads>
+__device__ __forceinline__ uint32_t slow_rounds(const DecodeArgs& a, ExpandSmem<kThreads>& sm, const BlockCtx& c,
+                                                uint32_t n_slow) {
+  constexpr uint32_t kR = ExpandSmem<kThreads>::kSlowRound;
+  const uint32_t tid = threadIdx.x;
+  const bool many = n_slow > kR;
+  uint32_t n_ext = 0;
+  if (many)
+    for (uint32_t j = tid; j < (n_slow + 31) / 32; j += kThreads) sm.deps[j] = 0;
+  lds_barrier();  // the pieces' tables are dead from here
+  for (uint32_t u0 = 0; u0 < n_slow; u0 += kR) {
+    uint32_t e[kSlowPer], pos[kSlowPer];
+    const uint32_t ub = u0 + kSlowPer * tid, un = ub < n_slow ? min(kSlowPer, n_slow - ub) : 0u;
+    uint32_t k = un ? slow_slot<kThreads>(sm, c, ub) : 0u;
+#pragma unroll
+    for (uint32_t j = 0; j < kSlowPer; j++) e[j] = pos[j] = 0;
+    // a run of bytes with consecutive sources of one kind per turn: most
+    // threads' bytes are one to three runs
+    for (uint32_t j0 = 0; j0 < un;) {
+      const uint32_t u = ub + j0;
+      while (sm.ptr[k] <= u) k++;  // on to the slot that holds byte u
+      const uint32_t Mk = sm.lm[k] >> 16, endk = sm.ptr[k], d = sm.dfl[k] & 0xFFFFFFu;
+      const uint32_t p = sm.dst[k] + (sm.lm[k] & 0xFFFFu) + (u - (endk - Mk));
+      uint32_t im, v = 0, val;
+      int32_t r;
+      const bool near = slow_source<kThreads>(sm, k, u, im, r);
+      uint32_t run = min(endk - u, Mk > d ? d - im : Mk);
+      bool prior = false;  // bytes of an earlier round, from v on
+      if (!near || r < 0) {
+        run = near ? min(run, (uint32_t)-r) : 1u;
+        val = kFromBlock | u;
+      } else if ((uint32_t)r < c.d0) {
+        run = min(run, c.d0 - (uint32_t)r);  // an earlier tile
+        val = (uint32_t)r;
+      } else {
+        const uint32_t q = (uint32_t)r, js = find_seq_before(sm.dst, k, q);
+        const uint32_t rr = q - sm.dst[js], Ls = sm.lm[js] & 0xFFFFu, Ms = sm.lm[js] >> 16, fl = sm.dfl[js] >> 24;
+        val = q;
+        if (rr < Ls) {
+          run = min(run, Ls - rr);
+        } else {
+          run = min(run, Ls + Ms > rr ? Ls + Ms - rr : 1u);
+          if (fl & kSlow) {
+            v = sm.ptr[js] - Ms + (rr - Ls);
+            prior = v < u0;
+            if (prior) run = min(run, u0 - v);
+            else val = kFromSlow | (v - u0);
+          } else if (fl & kExt) {
+            val |= kFromExt;
+          }
+        }
+      }
+#pragma unroll
+      for (uint32_t j = 0; j < kSlowPer; j++) {
+        if (j >= j0 && j < j0 + run) {
+          const uint32_t t = j - j0;
+          e[j] = val + t;
+          if (prior && ((sm.deps[(v + t) >> 5] >> ((v + t) & 31)) & 1)) e[j] |= kFromExt;
+          pos[j] = p + t;
+        }
+      }
+      j0 += run;
+    }
+    bool pend = false;
+#pragma unroll
+    for (uint32_t j = 0; j < kSlowPer; j++) {
+      sm.par[kSlowPer * tid + j] = e[j];
+      pend = pend || (e[j] & kFromSlow);
+    }
+    lds_barrier();
+    while (pend) {
+      pend = false;
+#pragma unroll
+      for (uint32_t j = 0; j < kSlowPer; j++) {
+        if (!(e[j] & kFromSlow)) continue;
+        e[j] = sm.par[(e[j] & kFromMask) % kR];
+        sm.par[kSlowPer * tid + j] = e[j];
+        pend = pend || (e[j] & kFromSlow);
+      }
+    }
+    __syncthreads();  // every byte read below has been stored; all chains are read
+    uint8_t v[kSlowPer];
+#pragma unroll
+    for (uint32_t j = 0; j < kSlowPer; j++) {
+      v[j] = 0;
+      if (ub + j >= n_slow) continue;
+      const uint8_t* q = c.out + (e[j] & kFromMask);
+      if (e[j] & kFromBlock) q = slow_ext_addr<kThreads>(a, sm, c, e[j] & kFromMask);
+      if (q) v[j] = ld8(q);
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < kSlowPer; j++) {
+      const uint32_t u = ub + j;
+      if (u >= n_slow) continue;
+      st8(c.out + pos[j], v[j]);
+      if (e[j] & (kFromExt | kFromBlock)) {
+        n_ext++;
+        if (many) atomicOr(&sm.deps[u >> 5], 1u << (u & 31));
+      }
+    }
+    if (many) lds_barrier();  // this round's bits before the next round reads them
+  }
+  return n_ext;
+}
+
 // 16 bytes from any byte address (one global load: this target's global
 // loads take any alignment).
 typedef u32x4 u32x4_a1 __attribute__((aligned(1)));
@@ -1100,6 +1271,7 @@ __device__ __forceinline__ void expand_block(const DecodeArgs& a, uint32_t i, Ex
   c.offs = offs;
   c.ow = a.ow;
   const bool cached = dep_cnt <= kDepCache;
+  bool deps_in = false;  // the cached list is in LDS
   uint32_t carry_pos = 0, carry_lit = 0, n_ext = 0;
   bool bad = false;
   // the piece marks start cleared (each thread clears the entries it later
@@ -1121,9 +1293,11 @@ __device__ __forceinline__ void expand_block(const DecodeArgs& a, uint32_t i, Ex
         O[h] = a.ow == 4 ? (uint64_t)ld32(offs + 4ull * k) : ld64(offs + 8ull * k);
       }
     }
-    if (t0 == 0) {
+    if (!deps_in) {
       // the block's dependency list, once, in LDS (issued after the first
-      // tile's token loads, so the latencies overlap)
+      // tile's token loads, so the latencies overlap); again when slow_rounds
+      // used its place
+      deps_in = true;
       for (uint32_t j = tid; j < (cached ? dep_cnt : 0u); j += kThreads) sm.deps[j] = deps[j];
     }
     // positions in sequence order: slots 0..kThreads-1 first, then the rest
@@ -1430,7 +1604,12 @@ __device__ __forceinline__ void expand_block(const DecodeArgs& a, uint32_t i, Ex
     // sequences, tiles or non-adjacent blocks), each thread an equal share of
     // consecutive ones, followed back to their origin (never to this tile's
     // output) a run of consecutive sources at a time
-    if (n_slow) {
+    if (n_slow > kSlowWalk * kThreads && n_slow <= 32 * kDepCache) {
+      n_ext += slow_rounds<kThreads>(a, sm, c, n_slow);
+      deps_in = n_slow <= ExpandSmem<kThreads>::kSlowRound;
+#pragma unroll
+      for (uint32_t j = 0; j < kPer; j++) sm.cseq[tid + j * kThreads] = 0;
+    } else if (n_slow) {
       const uint32_t per = (n_slow + kThreads - 1) / kThreads;
       uint32_t u = tid * per;
       const uint32_t u1 = min(u + per, n_slow);
