@@ -71,6 +71,9 @@ struct ace_archive {
   std::vector<PlanEntry> all_plan;
   std::vector<uint32_t> all_levels;
   uint64_t all_seq = 0;
+  // copy records of chained levels: per block, and the blocks recorded at a
+  // time (0: the archive has no run of small levels worth it)
+  uint32_t rec_cap = 0, chain_blocks = 0;
   PlanEntry* all_plan_pinned = nullptr;
   const PlanEntry* d_plan = nullptr;  // the whole-archive plan resident on the device, if attached
   const uint32_t* d_order = nullptr;  // with it: all blocks by level, then the level boundaries
@@ -222,6 +225,38 @@ static void level_order(const ace_archive* A, const std::vector<uint32_t>& block
   }
 }
 
+// Runs of small dependency levels are copied within one launch, from records
+// made ahead (launch_chain).  A level of up to kChainWidth blocks is small: the
+// chain copies 32 blocks of 16 KiB in about the 10 to 16 us that a launch of
+// its own takes a level whatever its size (a seek with three levels of 13 to
+// 20 blocks among 65: 500 us with a width of 12, 450 with 32, 450 with 100).  A
+// run of fewer than kChainRun levels does not pay for its two launches.
+constexpr uint32_t kChainWidth = 32, kChainRun = 3;
+constexpr uint64_t kChainBytes = 64ull << 20;  // records held at a time, at most
+
+// Consecutive levels that are expanded together: one level by its own launch,
+// or a chained run of at most max_blocks blocks.
+struct LevelRun {
+  uint32_t lo, hi;
+  bool chain;
+};
+static std::vector<LevelRun> level_runs(const std::vector<uint32_t>& lstart, uint32_t max_blocks) {
+  std::vector<LevelRun> runs;
+  uint32_t nl = lstart.empty() ? 0u : (uint32_t)lstart.size() - 1;
+  while (nl && lstart[nl] == lstart[nl - 1]) nl--;  // a plan's closure may end below the archive's last level
+  for (uint32_t l = 0; l < nl;) {
+    uint32_t e = l;
+    while (e < nl && lstart[e + 1] - lstart[e] <= kChainWidth && lstart[e + 1] - lstart[l] <= max_blocks &&
+           e + 1 - l <= max_blocks)
+      e++;
+    const bool chain = e - l >= kChainRun;
+    if (!chain) e = l + 1;
+    runs.push_back(LevelRun{l, e, chain});
+    l = e;
+  }
+  return runs;
+}
+
 extern "C" int ace_archive_open(const uint8_t* h_arch, uint64_t len, const void* d_arch,
                                 ace_archive** out) {
   if (!h_arch || !out) return fail(ACE_E_ARG, "null argument");
@@ -248,6 +283,14 @@ extern "C" int ace_archive_open(const uint8_t* h_arch, uint64_t len, const void*
     return fail(ACE_E_CORRUPT, "more than 2^32 sequences");
   }
   A->all_seq = seq;
+  // records per block: what 16-byte pieces of a block need, twice over, and
+  // some for its runs of straddling bytes (a block that needs more is expanded
+  // without records)
+  A->rec_cap = A->B / 8 + 512;
+  uint32_t fit = (uint32_t)std::min<uint64_t>(kChainBlocks, kChainBytes / (16ull * A->rec_cap));
+  if (A->rec_cap > kMaxRecs) fit = 0;
+  for (const LevelRun& r : level_runs(A->all_levels, fit))
+    if (r.chain) A->chain_blocks = fit;
   *out = A;
   return ACE_OK;
 }
@@ -382,8 +425,29 @@ constexpr uint32_t kModePersistent = 2, kModeOverlap = 3;  // 0 and 1: per level
 constexpr uint32_t kMaxIdlePolls = 1u << 21;
 
 struct Layout {
-  uint64_t plan, lv, loc, lit, lens, offs, slots, items, total;
+  uint64_t plan, lv, loc, lit, lens, offs, slots, items, base;  // base: the bytes without copy records
+  uint64_t ends, sync, recs, total;
 };
+
+// The copy records of chained levels, at the end of a workspace.
+template <typename L>
+void layout_records(const ace_archive* A, uint64_t n_plan, L& l, uint64_t o) {
+  const uint64_t nb = std::min<uint64_t>(A->chain_blocks, n_plan);
+  l.base = o;
+  l.ends = o;  o = align_up(o + 4ull * kChainEnds * nb, 256);
+  l.sync = o;  o = align_up(o + (nb ? 4ull * kChainSync : 0), 256);
+  l.recs = o;  o = align_up(o + 16ull * A->rec_cap * nb, 256);
+  l.total = o;
+}
+template <typename L>
+ChainArgs chain_args(const ace_archive* A, const L& l, uint8_t* ws) {
+  ChainArgs c;
+  c.recs = ws + l.recs;
+  c.ends = reinterpret_cast<uint32_t*>(ws + l.ends);
+  c.sync = reinterpret_cast<uint32_t*>(ws + l.sync);
+  c.rec_cap = A->rec_cap;
+  return c;
+}
 
 // Workspace of one host-planned decode.  lv: per dependency level of the
 // archive, the plan's level boundaries (depth + 1), then the persistent
@@ -400,7 +464,7 @@ Layout layout(const ace_archive* A, uint64_t n_plan, uint64_t n_seq, uint64_t n_
   L.offs = o;  o = align_up(o + (uint64_t)A->ow * n_seq, 256);
   L.slots = o; o = align_up(o + (uint64_t)A->B * n_slots, 256);
   L.items = o; o = align_up(o + sizeof(CopyItem) * n_items, 256);
-  L.total = o;
+  layout_records(A, n_plan, L, o);
   return L;
 }
 
@@ -456,23 +520,24 @@ void close_range(const ace_archive* A, uint32_t t0, uint32_t t1, std::vector<uin
 static int run_launches(const ace_archive* A, const PlanEntry* entries, uint64_t n_plan,
                         const std::vector<uint32_t>& lstart, const CopyItem* items, uint64_t n_items,
                         const Layout& L, uint8_t* ws, uint64_t dst_base, const ace_tuning* t,
-                        hipStream_t s, bool entries_pinned, bool loc_linear,
+                        hipStream_t s, bool chain, bool loc_linear,
                         const PlanEntry* resident, const uint8_t* arch);
 
-// Runs a host-built plan; with phase timing on, also records the host time
+// Runs a host-built plan (chain: runs of small levels may be chained, the
+// workspace holds L.total bytes); with phase timing on, also records the host time
 // spent planning (since the call's entry) and enqueueing.
 static int run(const ace_archive* A, const PlanEntry* entries, uint64_t n_plan,
                const std::vector<uint32_t>& lstart, const CopyItem* items, uint64_t n_items,
                const Layout& L, uint8_t* ws, uint64_t dst_base, const ace_tuning* t,
-               hipStream_t s, bool entries_pinned, bool loc_linear = false,
+               hipStream_t s, bool chain, bool loc_linear = false,
                const PlanEntry* resident = nullptr, const uint8_t* arch = nullptr) {
   if (!g_timer.on)
-    return run_launches(A, entries, n_plan, lstart, items, n_items, L, ws, dst_base, t, s, entries_pinned,
+    return run_launches(A, entries, n_plan, lstart, items, n_items, L, ws, dst_base, t, s, chain,
                         loc_linear, resident, arch);
   const auto t_run = std::chrono::steady_clock::now();
   g_timer.us_plan = std::chrono::duration<double, std::micro>(t_run - g_timer.t_enter).count();
   const int rc = run_launches(A, entries, n_plan, lstart, items, n_items, L, ws, dst_base, t, s,
-                              entries_pinned, loc_linear, resident, arch);
+                              chain, loc_linear, resident, arch);
   g_timer.us_enqueue = us_since(t_run);
   return rc;
 }
@@ -480,9 +545,8 @@ static int run(const ace_archive* A, const PlanEntry* entries, uint64_t n_plan,
 static int run_launches(const ace_archive* A, const PlanEntry* entries, uint64_t n_plan,
                         const std::vector<uint32_t>& lstart, const CopyItem* items, uint64_t n_items,
                         const Layout& L, uint8_t* ws, uint64_t dst_base, const ace_tuning* t,
-                        hipStream_t s, bool entries_pinned, bool loc_linear,
+                        hipStream_t s, bool chain, bool loc_linear,
                         const PlanEntry* resident, const uint8_t* arch) {
-  (void)entries_pinned;
   if (!arch) arch = A->d_arch;  // an out-of-core seek passes its staged copy
   const uint32_t mode = t ? t->mode : 0;
   if (mode > 1 && mode != kModeOverlap && mode != kModePersistent) return fail(ACE_E_ARG, "unknown mode %u", mode);
@@ -577,8 +641,32 @@ static int run_launches(const ace_archive* A, const PlanEntry* entries, uint64_t
       HIP_TRY(hipStreamWaitEvent(s, o->ev[1], 0));
       for (size_t l = split; l < nl; l++) HIP_TRY(expand(l));
     } else {
+      std::vector<LevelRun> runs;
+      if (chain && A->chain_blocks && waves == 0)
+        runs = level_runs(lstart, (uint32_t)std::min<uint64_t>(A->chain_blocks, n_plan));
+      const bool chained = std::any_of(runs.begin(), runs.end(), [](const LevelRun& r) { return r.chain; });
+      if (chained) {  // the kernels read the level boundaries on the device
+        if (resident)
+          a.lvl_dev = A->d_lstart;
+        else
+          HIP_TRY(hipMemcpyAsync(ws + L.lv, lstart.data(), 4ull * lstart.size(), hipMemcpyHostToDevice, s));
+      }
       HIP_TRY(entropy(0, (uint32_t)n_plan, s));
-      for (size_t l = 0; l < nl; l++) HIP_TRY(expand(l));
+      if (!chained)
+        for (size_t l = 0; l < nl; l++) HIP_TRY(expand(l));
+      else
+        for (const LevelRun& r : runs) {
+          if (!r.chain) {
+            HIP_TRY(expand(r.lo));
+            continue;
+          }
+          if (timed) {
+            HIP_TRY(timer_pair(T.mat, T.n_mat));
+            HIP_TRY(hipEventRecord(T.mat[2 * T.n_mat], s));
+          }
+          HIP_TRY(launch_chain(a, chain_args(A, L, ws), r.lo, r.hi, lstart[r.hi] - lstart[r.lo], s));
+          if (timed) HIP_TRY(hipEventRecord(T.mat[2 * T.n_mat++ + 1], s));
+        }
     }
     T.recorded = timed;
   }
@@ -627,7 +715,7 @@ extern "C" int ace_decode_all(const ace_archive* A, uint8_t* d_out, uint64_t out
   if (A->nb == 0) return ACE_OK;
   if (A->d_plan)
     return run(A, A->all_plan.data(), A->nb, A->all_levels, nullptr, 0, L, static_cast<uint8_t*>(d_ws),
-               (uint64_t)(uintptr_t)d_out, t, static_cast<hipStream_t>(stream), false, true, A->d_plan);
+               (uint64_t)(uintptr_t)d_out, t, static_cast<hipStream_t>(stream), true, true, A->d_plan);
   ace_archive* M = const_cast<ace_archive*>(A);
   const PlanEntry* entries = A->all_plan.data();
   {
@@ -730,8 +818,11 @@ static int seek_impl(const ace_archive* A, uint64_t lo, uint64_t hi, uint8_t* d_
     items.push_back(CopyItem{s0, (uint64_t)(uintptr_t)d_out + (s0 - lo), (uint32_t)(s1 - s0), 0});
   }
   Layout L = layout(A, order.size(), seq, n_slots, items.size());
-  if (ws_need) *ws_need = L.total;
-  if (ws_cap < L.total) return fail(ACE_E_NOSPACE, "workspace needs %llu bytes", (unsigned long long)L.total);
+  // the allocation-free seek has a fixed scratch and may be captured: it keeps
+  // to a launch per level, without copy records
+  const uint64_t needs = allow_device ? L.total : L.base;
+  if (ws_need) *ws_need = needs;
+  if (ws_cap < needs) return fail(ACE_E_NOSPACE, "workspace needs %llu bytes", (unsigned long long)needs);
   uint8_t* ws = static_cast<uint8_t*>(d_ws);
   uint64_t slot = 0;
   for (size_t i = 0; i < order.size(); i++) {
@@ -740,7 +831,7 @@ static int seek_impl(const ace_archive* A, uint64_t lo, uint64_t hi, uint8_t* d_
                                : (uint64_t)(uintptr_t)(ws + L.slots) + (slot++) * A->B;
   }
   return run(A, entries.data(), entries.size(), lstart, items.data(), items.size(), L, ws, 0, t,
-             static_cast<hipStream_t>(stream), false);
+             static_cast<hipStream_t>(stream), allow_device);
 }
 
 extern "C" int ace_seek(const ace_archive* A, uint64_t lo, uint64_t hi, uint8_t* d_out, void* d_ws,
@@ -881,7 +972,7 @@ extern "C" int ace_seek_ooc(const ace_archive* A, uint64_t lo, uint64_t hi, uint
   }
   if (staged > sent) HIP_TRY(hipMemcpyAsync(ws + P.stage + sent, h + sent, staged - sent, hipMemcpyHostToDevice, s));
   const int rc = run(A, P.entries.data(), P.entries.size(), P.lstart, P.items.data(), P.items.size(), P.L, ws, 0,
-                     t, s, false, false, nullptr, ws + P.stage - P.gap);
+                     t, s, true, false, nullptr, ws + P.stage - P.gap);
   if (rc) return rc;
   HIP_TRY(hipStreamSynchronize(s));
   return ACE_OK;
@@ -952,7 +1043,7 @@ extern "C" int ace_seek_batch(const ace_archive* A, const ace_range* r, uint32_t
     sq += A->blk[order[i]].n_seq;
   }
   return run(A, entries.data(), entries.size(), lstart, items.data(), items.size(), L, ws, 0, t,
-             static_cast<hipStream_t>(stream), false);
+             static_cast<hipStream_t>(stream), true);
 }
 
 extern "C" int ace_check(void* d_ws, void* stream) {
@@ -1005,7 +1096,7 @@ struct ace_batch {
 namespace {
 struct BatchLayout {
   uint64_t order, lstart, need, pre, plan, nplan, lvl, loc, lit, lens, offs, slots, desc, pin, pinbase,
-      chunks, total;
+      chunks, base, ends, sync, recs, total;
 };
 
 BatchLayout batch_layout(const ace_archive* A, uint32_t cap) {
@@ -1032,8 +1123,28 @@ BatchLayout batch_layout(const ace_archive* A, uint32_t cap) {
   L.pin = take(align_up(A->nb, 4));
   L.pinbase = take(4);
   L.chunks = take(8ull * (batch_compact_chunks(A->nb) + 1));
-  L.total = o;
+  layout_records(A, A->nb, L, o);
   return L;
+}
+
+// The expansion launches of a device-planned decode, level by level, runs of
+// small levels chained.
+// Level sizes are read on the device; the archive's bound them.
+hipError_t expand_levels_dev(const ace_archive* A, const DecodeArgs& a, const BatchLayout& L, uint8_t* ws,
+                             bool chain, uint32_t waves, hipStream_t s) {
+  const std::vector<uint32_t>& lv = A->all_levels;
+  std::vector<LevelRun> runs;
+  if (chain && A->chain_blocks && waves == 0)
+    runs = level_runs(lv, std::min(A->chain_blocks, A->nb));
+  else
+    for (uint32_t l = 0; l < A->depth; l++) runs.push_back(LevelRun{l, l + 1, false});
+  hipError_t e = hipSuccess;
+  for (const LevelRun& r : runs) {
+    e = r.chain ? launch_chain(a, chain_args(A, L, ws), r.lo, r.hi, lv[r.hi] - lv[r.lo], s)
+                : launch_expand_level_dev(a, r.lo, lv[r.hi] - lv[r.lo], waves, s);
+    if (e != hipSuccess) break;
+  }
+  return e;
 }
 }  // namespace
 
@@ -1137,8 +1248,7 @@ static int seek_device(const ace_archive* A, uint64_t lo, uint64_t hi, uint8_t* 
       HIP_TRY(hipEventRecord(T.ent[1], s));
       HIP_TRY(hipEventRecord(T.mat[0], s));
     }
-    for (uint32_t l = 0; l < A->depth; l++)
-      HIP_TRY(launch_expand_level_dev(a, l, A->all_levels[l + 1] - A->all_levels[l], waves, s));
+    HIP_TRY(expand_levels_dev(A, a, L, ws, mode <= 1, waves, s));
   }
   if (timed) HIP_TRY(hipEventRecord(T.mat[1], s));
   HIP_TRY(launch_batch_gather(ba, a, hi - lo, s));
@@ -1327,8 +1437,7 @@ extern "C" int ace_batch_create(const ace_archive* A, uint32_t cap, void* d_ws, 
       }
     } else if (e == hipSuccess) {
       e = launch_rans_dev(a, A->nb, per_wave, s);
-      for (uint32_t l = 0; e == hipSuccess && l < A->depth; l++)
-        e = launch_expand_level_dev(a, l, A->all_levels[l + 1] - A->all_levels[l], waves, s);
+      if (e == hipSuccess) e = expand_levels_dev(A, a, L, b->ws, true, waves, s);
     }
     if (e == hipSuccess) e = launch_batch_gather(ba, a, 0, s);
     hipError_t e2 = hipStreamEndCapture(s, &b->graph);

@@ -706,7 +706,7 @@ struct ExpandSmem {
   uint32_t win[kSeq];     // readable bytes around src0: back (0..31) | forward << 5; unresolved: O - block start
   uint32_t ptr[kSeq];     // pending span: span of sequence (ptr >> 16) from offset (ptr & 0xFFFF)
   uint32_t deps[kDepCache];
-  uint32_t scan[kPer * kThreads / 64 > 32 ? kPer * kThreads / 64 : 32];
+  uint32_t scan[32];  // a workgroup's scans: at most four words per wavefront, eight wavefronts
 };
 
 // A workgroup barrier that orders LDS accesses only: global loads and stores
@@ -885,6 +885,16 @@ __device__ __forceinline__ uint32_t orel_pack(uint64_t o, uint64_t bs) {
   return r > -(int64_t)0x7FFFFFFF && r < (int64_t)0x7FFFFFFF ? (uint32_t)(int32_t)r : kOrelFar;
 }
 
+// Readable bytes around a resolved span's address: back (capped at 31) and
+// forward (capped at 2^26).
+__device__ __forceinline__ uint32_t win_pack(uint64_t back, uint64_t fwd) {
+  return (uint32_t)(back < 31 ? back : 31) | ((uint32_t)(fwd < (1ull << 26) ? fwd : (1ull << 26)) << 5);
+}
+// Around literal lp of the block: literal streams have readable slack.
+__device__ __forceinline__ uint32_t lit_win(const BlockCtx& c, uint32_t lp) {
+  return win_pack(lp, (uint64_t)(c.n_lit - lp) + 4);
+}
+
 // Slow path: the address of the byte at block-relative p, following sources
 // back to a literal, a resolved span, an earlier tile of this block or an
 // earlier block (each step moves strictly backwards, so the walk ends), and
@@ -893,13 +903,14 @@ __device__ __forceinline__ uint32_t orel_pack(uint64_t o, uint64_t bs) {
 // period's wrap, the earlier tiles' end and the current block's start).
 // Null when the bytes are to be written as zeros (a failed format rule, or an
 // earlier block that was never published).  ext: the address lies in an
-// earlier block.  Reads LDS and (outside whole-archive decodes, or for
+// earlier block.  win: the readable bytes around the address (win_pack).  Reads LDS and (outside whole-archive decodes, or for
 // offsets too far back) the location table and the offset stream.
 template <uint32_t kThreads>
 __device__ const uint8_t* resolve_run(const DecodeArgs& a, const ExpandSmem<kThreads>& sm, const BlockCtx& c,
-                                      uint32_t s, uint32_t p, uint32_t& run, bool& ext) {
+                                      uint32_t s, uint32_t p, uint32_t& run, bool& ext, uint32_t& win) {
   uint32_t lim = 0xFFFFFFFFu;
   ext = false;
+  win = 0;
   for (;;) {
     const uint32_t fl = sm.dfl[s] >> 24;
     const uint32_t r = p - sm.dst[s];
@@ -910,6 +921,7 @@ __device__ const uint8_t* resolve_run(const DecodeArgs& a, const ExpandSmem<kThr
     }
     if (r < Ls) {
       run = min(lim, Ls - r);
+      win = lit_win(c, sm.lit[s] + r);
       return c.lit + sm.lit[s] + r;
     }
     const uint32_t ii = r - Ls, d = sm.dfl[s] & 0xFFFFFFu;
@@ -918,6 +930,7 @@ __device__ const uint8_t* resolve_run(const DecodeArgs& a, const ExpandSmem<kThr
     if (!(fl & kUnres)) {
       run = lim;
       ext = (fl & kExt) != 0;
+      win = win_pack((sm.win[s] & 31u) + im, (sm.win[s] >> 5) - im);
       return reinterpret_cast<const uint8_t*>(sm.src0[s] + im);
     }
     // the source offset, kept beside the sequence (read back from the token
@@ -936,11 +949,13 @@ __device__ const uint8_t* resolve_run(const DecodeArgs& a, const ExpandSmem<kThr
       const uint64_t room = a.loc_linear ? c.bs - src : (blk + 1) * a.B - src;  // contiguous bytes there
       run = (uint32_t)min((uint64_t)lim, room);
       ext = true;
+      win = win_pack(src - blk * a.B, room);
       return reinterpret_cast<const uint8_t*>(blk_loc(a, blk)) + (src - blk * a.B);
     }
     const uint32_t q = (uint32_t)(src - c.bs);
     if (q < c.d0) {
       run = min(lim, c.d0 - q);
+      win = win_pack(q, c.blen - q);
       return c.out + q;
     }
     s = find_seq_before(sm.dst, s, q);  // the source lies before this sequence
@@ -1230,12 +1245,6 @@ __device__ __forceinline__ void copy_range(const DecodeArgs& a, const uint64_t* 
   }
 }
 
-// Readable bytes around a resolved span's address: back (capped at 31) and
-// forward (capped at 2^26).
-__device__ __forceinline__ uint32_t win_pack(uint64_t back, uint64_t fwd) {
-  return (uint32_t)(back < 31 ? back : 31) | ((uint32_t)(fwd < (1ull << 26) ? fwd : (1ull << 26)) << 5);
-}
-
 // Output pieces of a match of m bytes (m < 2^16) whose byte i is span byte
 // i mod d: a match that repeats its span (m > d) with d >= 16 is cut period
 // by period, each period into 16-byte pieces from its start; any other match
@@ -1246,11 +1255,39 @@ __device__ __forceinline__ uint32_t match_pieces(uint32_t m, uint32_t d) {
   return q * ((d + 15) >> 4) + ((m - q * d + 15) >> 4);
 }
 
+// A copy record: one output piece with its source resolved, made ahead of the
+// copy (kPrep below).  src and dst are 48-bit device addresses.
+//   x, y: src | len (1..16) << 48 | shift << 53 | kind << 58
+//   z, w: dst | period << 48 | first << 52
+// kCopy: 16 bytes are loaded from src and moved down by shift; with a period
+// (1..15), byte i of the piece is byte (first + i) mod period of those.
+// kZero: zeros.  kBytes: byte i is read at src + (first + i) mod period (src +
+// i without a period), where 16 bytes around src are not known readable.
+constexpr uint32_t kCopy = 0, kZero = 1, kBytes = 2;
+__device__ __forceinline__ uint4 make_rec(uint64_t src, uint64_t dst, uint32_t len, uint32_t shift, uint32_t kind,
+                                          uint32_t period, uint32_t first) {
+  return make_uint4((uint32_t)src, ((uint32_t)(src >> 32) & 0xFFFFu) | (len << 16) | (shift << 21) | (kind << 26),
+                    (uint32_t)dst, ((uint32_t)(dst >> 32) & 0xFFFFu) | (period << 16) | (first << 20));
+}
+
+// Where kPrep puts a block's records: rec[0 .. cap), those of tile t ending at
+// ends[1 + t]; ends[0] the tiles (kUnprepared: the records or the tiles did not
+// fit, the block is expanded when its turn comes).
+constexpr uint32_t kPrepTiles = 7, kUnprepared = 0xFFu;
+struct PrepOut {
+  uint4* rec;
+  uint32_t cap;
+  uint32_t* ends;
+  uint32_t* n;  // LDS: records of the block so far
+};
+
 // Expands plan entry i with kThreads threads.  Sources in earlier blocks must
 // be complete and visible (unless ext_ok is false, after a timed-out wait).
-template <uint32_t kThreads>
+// kPrep: writes the block's copy records instead of its bytes (reads no
+// decoded bytes, so it needs no earlier block to be complete).
+template <uint32_t kThreads, bool kPrep = false>
 __device__ __forceinline__ void expand_block(const DecodeArgs& a, uint32_t i, ExpandSmem<kThreads>& sm,
-                                             bool ext_ok = true) {
+                                             bool ext_ok = true, const PrepOut* po = nullptr) {
   constexpr uint32_t kSeq = ExpandSmem<kThreads>::kSeq, kRound = ExpandSmem<kThreads>::kRound;
   const uint32_t tid = threadIdx.x;
   const PlanEntry pe = a.plan[i];
@@ -1279,7 +1316,8 @@ __device__ __forceinline__ void expand_block(const DecodeArgs& a, uint32_t i, Ex
   // barriers of the token phase
 #pragma unroll
   for (uint32_t j = 0; j < kPer; j++) sm.cseq[tid + j * kThreads] = 0;
-  for (uint32_t t0 = 0; t0 < n_seq; t0 += kSeq) {
+  uint32_t rec0 = 0, tile = 0, tiles = 0;  // kPrep: records before this tile; tiles recorded
+  for (uint32_t t0 = 0; t0 < n_seq; t0 += kSeq, tile++) {
     // ---- two sequences per thread: tokens, scans, first classification
     uint32_t L[2] = {0, 0}, M[2] = {0, 0};
     uint64_t O[2] = {0, 0};
@@ -1402,7 +1440,7 @@ __device__ __forceinline__ void expand_block(const DecodeArgs& a, uint32_t i, Ex
       if (j_ok && r + sl <= Lj) {
         const uint32_t lp = sm.lit[j] + r;
         src0 = (uint64_t)(uintptr_t)(c.lit + lp);
-        win = win_pack(lp, (uint64_t)(c.n_lit - lp) + 4);  // literal streams have readable slack
+        win = lit_win(c, lp);
         fl = 0;
       } else if (j_ok && r >= Lj) {
         const uint32_t off = r - Lj, dj = sm.dfl[j] & 0xFFFFFFu;
@@ -1569,6 +1607,28 @@ __device__ __forceinline__ void expand_block(const DecodeArgs& a, uint32_t i, Ex
             A1 = c.lit;
           }
         }
+        if (kPrep) {
+          if (on && rec0 + p < po->cap) {
+            const bool lit_piece = (fl & kPoison) || k < pl;
+            uint64_t src = (uint64_t)(uintptr_t)A1;
+            uint32_t sh = s1, kind = kCopy, period = 0, first = 0;
+            if (!lit_piece && Ms > dist && dist < 16) {
+              const uint32_t back = wn & 31u, fwd = wn >> 5;
+              period = dist;
+              first = off % dist;
+              sh = fwd < 16 ? 16 - fwd : 0u;
+              kind = sh > back ? kBytes : kCopy;
+              src = kind == kBytes ? s0 : s0 - sh;
+            } else if (s1 == 0xFFu) {
+              kind = kBytes;
+              src = s0 + at;
+            }
+            if (zero) kind = kZero;
+            po->rec[rec0 + p] = make_rec(src, (uint64_t)(uintptr_t)(c.out + dsto[j]), r, kind == kCopy ? sh : 0u, kind,
+                                         period, first);
+          }
+          continue;
+        }
         len[j] = on ? r : 0u;
         sh1[j] = zero ? 0x100u : s1;  // 0x100: zeros
         v1[j] = ld16u(zero || s1 == 0xFFu ? c.lit : A1);
@@ -1588,7 +1648,7 @@ __device__ __forceinline__ void expand_block(const DecodeArgs& a, uint32_t i, Ex
       // assemble and store: the load shifted down by sh1 (or zeros);
       // exactly len bytes written
 #pragma unroll
-      for (uint32_t j = 0; j < kPer; j++) {
+      for (uint32_t j = 0; j < (kPrep ? 0 : kPer); j++) {
         if (!len[j]) continue;
         uint32_t w[4] = {v1[j].x, v1[j].y, v1[j].z, v1[j].w};
         if (sh1[j] == 0x100u) {
@@ -1604,7 +1664,11 @@ __device__ __forceinline__ void expand_block(const DecodeArgs& a, uint32_t i, Ex
     // sequences, tiles or non-adjacent blocks), each thread an equal share of
     // consecutive ones, followed back to their origin (never to this tile's
     // output) a run of consecutive sources at a time
-    if (n_slow > kSlowWalk * kThreads && n_slow <= 32 * kDepCache) {
+    if (kPrep) {
+      if (tid == 0) *po->n = rec0 + n_piece;
+      lds_barrier();
+    }
+    if (!kPrep && n_slow > kSlowWalk * kThreads && n_slow <= 32 * kDepCache) {
       n_ext += slow_rounds<kThreads>(a, sm, c, n_slow);
       deps_in = n_slow <= ExpandSmem<kThreads>::kSlowRound;
 #pragma unroll
@@ -1617,12 +1681,21 @@ __device__ __forceinline__ void expand_block(const DecodeArgs& a, uint32_t i, Ex
       while (u < u1) {
         const uint32_t Mk = sm.lm[k] >> 16, end_k = sm.ptr[k];
         const uint32_t p = sm.dst[k] + (sm.lm[k] & 0xFFFFu) + (u - (end_k - Mk));
-        uint32_t run;
+        uint32_t run, win;
         bool ext;
-        const uint8_t* q = resolve_run<kThreads>(a, sm, c, k, p, run, ext);
+        const uint8_t* q = resolve_run<kThreads>(a, sm, c, k, p, run, ext, win);
         const uint32_t n = min(min(run, u1 - u), end_k - u);
         if (ext) n_ext += n;
-        for (uint32_t i = 0; i < n; i += 4) {
+        for (uint32_t i = 0; kPrep && i < n; i += 16) {
+          const uint32_t len = n - i < 16 ? n - i : 16u, slot = atomicAdd(po->n, 1u);
+          const uint32_t back = (win & 31u) + i, fwd = (win >> 5) > i ? (win >> 5) - i : 0u;
+          const uint32_t sh = fwd < 16 ? 16 - fwd : 0u;
+          const uint32_t kind = !q ? kZero : sh > back ? kBytes : kCopy;
+          const uint64_t src = (uint64_t)(uintptr_t)q + i - (kind == kCopy ? sh : 0u);
+          if (slot < po->cap)
+            po->rec[slot] = make_rec(src, (uint64_t)(uintptr_t)(c.out + p + i), len, kind == kCopy ? sh : 0u, kind, 0, 0);
+        }
+        for (uint32_t i = 0; !kPrep && i < n; i += 4) {
           uint8_t v[4];
 #pragma unroll
           for (uint32_t j = 0; j < 4; j++) v[j] = (q && i + j < n) ? ld8(q + i + j) : (uint8_t)0;
@@ -1633,6 +1706,12 @@ __device__ __forceinline__ void expand_block(const DecodeArgs& a, uint32_t i, Ex
         u += n;
         while (u < u1 && sm.ptr[k] <= u) k++;  // on to the next slow slot
       }
+    }
+    if (kPrep) {
+      lds_barrier();  // every record of the tile is counted
+      rec0 = *po->n;
+      if (tid == 0 && tile < kPrepTiles) po->ends[1 + tile] = rec0;
+      tiles = tile + 1;
     }
     // the next tile reads this tile's output and rewrites the tables
     if (t0 + kSeq < n_seq) __syncthreads();
@@ -1645,6 +1724,11 @@ __device__ __forceinline__ void expand_block(const DecodeArgs& a, uint32_t i, Ex
   }
   if (tid == 0 && (carry_pos != c.blen || carry_lit > c.n_lit)) bad = true;
   if (bad) flag(a.err, kErrCorrupt);
+  if (kPrep) {
+    const bool fits = rec0 <= po->cap && tiles <= kPrepTiles;
+    if (tid == 0) po->ends[0] = fits ? tiles : kUnprepared;
+    if (!fits) return;  // counted when it is expanded
+  }
   // one counter update per block, spread over 16 counters
   n_ext = wave_total(n_ext);
   lds_barrier();
@@ -1676,6 +1760,282 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kThrea
       a.trace[8ull * i + 1] = (unsigned long long)wall_clock64();
     }
     if (i + stride < end) lds_barrier();  // every thread done with this block's LDS tables
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Chains of small dependency levels.
+//
+// An archive without a level cap has hundreds to thousands of levels of a few
+// blocks.  A launch per level costs each one block's whole latency (token
+// scans, classification, pointer doubling, walks: 8 to 15 us) and a launch.
+// Of that work only the copies need the levels below, so a run of small
+// levels takes two launches: k_prep turns every block of the run into copy
+// records at once, and k_chain copies level after level with a few workgroups
+// of one XCD.  Their stores meet in that XCD's L2, so a level is handed on by
+// a counter in memory without the L2 writeback that workgroups on different
+// XCDs would need.
+//
+// What bounds a level is a load's and a store's latency and the hand-over,
+// about 3.5 us (a counter at agent scope instead of in the L2, and every wave
+// dropping the vector cache, made it 6.5 us).  One workgroup alone (no
+// hand-over) is bounded by its CU's address processing, some 340 cycles per
+// 64 records (scattered 16-byte loads and stores): 8.6 us for a level of three
+// 16 KiB blocks.  A thread's records of the next level are loaded while this
+// one is copied.  Whole decodes, a launch per level before: 12 MiB mixed of 192
+// levels 3.10 -> 0.69 ms, 1 MiB genome of 27 levels 0.51 -> 0.18 ms, 6 MiB
+// FASTQ 4.05 -> 0.85 ms, 6 MiB text in 64 KiB blocks 6.5 -> 0.82 ms.
+// ---------------------------------------------------------------------------
+constexpr uint32_t kPrepThreads = 512, kChainThreads = 512, kChainPer = 1;
+
+__global__ __launch_bounds__(kPrepThreads) void k_prep(DecodeArgs a, ChainArgs ch, uint32_t lv_lo, uint32_t lv_hi) {
+  __shared__ ExpandSmem<kPrepThreads> sm;
+  __shared__ uint32_t n_rec;
+  // the following k_chain's counters
+  if (blockIdx.x == 0 && threadIdx.x < kChainSync) ch.sync[threadIdx.x] = 0;
+  const uint32_t i = a.lvl_dev[lv_lo] + blockIdx.x;
+  if (i >= a.lvl_dev[lv_hi]) return;
+  PrepOut po;
+  po.rec = reinterpret_cast<uint4*>(ch.recs) + (uint64_t)blockIdx.x * ch.rec_cap;
+  po.cap = ch.rec_cap;
+  po.ends = ch.ends + (uint64_t)blockIdx.x * kChainEnds;
+  po.n = &n_rec;
+  if (threadIdx.x == 0) n_rec = 0;
+  expand_block<kPrepThreads, true>(a, i, sm, true, &po);
+}
+
+// The bytes of record r (see make_rec), to be moved down by its shift; a
+// kBytes record is read here, byte by byte.
+__device__ __forceinline__ uint4 rec_load(uint4 r, bool on) {
+  const uint32_t kind = on ? r.y >> 26 : kZero;
+  const uint8_t* src = reinterpret_cast<const uint8_t*>((uint64_t)r.x | ((uint64_t)(r.y & 0xFFFFu) << 32));
+  uint4 v = make_uint4(0, 0, 0, 0);
+  if (kind == kCopy) v = ld16u(src);
+  if (kind == kBytes) {
+    const uint32_t len = (r.y >> 16) & 31u, period = (r.w >> 16) & 15u;
+    uint32_t w[4] = {0, 0, 0, 0}, at = period ? (r.w >> 20) & 15u : 0u;
+#pragma unroll
+    for (uint32_t i = 0; i < 16; i++) {
+      if (i < len) w[i >> 2] |= (uint32_t)ld8(src + at) << (8 * (i & 3));
+      at = at + 1 == period ? 0u : at + 1;
+    }
+    v = make_uint4(w[0], w[1], w[2], w[3]);
+  }
+  return v;
+}
+
+__device__ __forceinline__ void rec_store(uint4 r, uint4 v) {
+  const uint32_t len = (r.y >> 16) & 31u, shift = (r.y >> 21) & 31u, kind = r.y >> 26, period = (r.w >> 16) & 15u;
+  uint8_t* dst = reinterpret_cast<uint8_t*>((uint64_t)r.z | ((uint64_t)(r.w & 0xFFFFu) << 32));
+  uint32_t w[4] = {v.x, v.y, v.z, v.w};
+  if (shift) shift_down16(w, shift);
+  if (kind == kCopy && period) {  // byte i is byte (first + i) mod period of the span
+    uint32_t o[4] = {0, 0, 0, 0}, at = (r.w >> 20) & 15u;
+#pragma unroll
+    for (uint32_t i = 0; i < 16; i++) {
+      const uint32_t q = at >> 2, x = q == 0 ? w[0] : q == 1 ? w[1] : q == 2 ? w[2] : w[3];
+      o[i >> 2] |= ((x >> (8 * (at & 3))) & 0xFFu) << (8 * (i & 3));
+      at = at + 1 == period ? 0u : at + 1;
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < 4; i++) w[i] = o[i];
+  }
+  store_bytes(dst, w, len);
+}
+
+// The XCD (accelerator complex die) this wave runs on: the XCC_ID hardware
+// register, bits 3:0.
+__device__ __forceinline__ uint32_t xcc_id() {
+  return __builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 20) & (kMaxXcc - 1);
+}
+
+// A counter shared across workgroups, read at agent scope.
+__device__ __forceinline__ uint32_t coherent_u32(const uint32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Adds to a counter that only workgroups of one XCD use while the kernel runs
+// (read-modify-write operations of a scope within the XCD take place in its
+// L2), and returns what it held: a tenth of an agent-scope one's time with
+// eight workgroups at it, whose counter is in memory.
+__device__ __forceinline__ uint32_t l2_add(uint32_t* p, uint32_t v) {
+  ACE_OPAQUE(v);  // adding 0, to read it, must not become a load (which may hit the CU's own cache)
+  return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// One of kMaxXcc times the wanted members: the workgroups on the XCD that the
+// first one to arrive runs on become the members, the others end.  Member 0
+// closes the door once every workgroup of the launch has arrived (or after
+// kDoorPolls idle polls, so that the launch needs no co-residency), and says
+// how many members there are.  Counters in sync, one per 128-byte line: the
+// XCD + 1; members so far, and kClosed; workgroups arrived; the members, once
+// closed; steps finished, summed over the members.  Thread 0 only: the
+// member's rank and the count in n, or kNoItem.
+// kChainPolls: consecutive idle polls before a wait gives up, in units of the
+// persistent kernel's (a chain polls about four times as often).
+constexpr uint32_t kClosed = 1u << 31, kDoorPolls = 512, kNoItem = 0xffffffffu, kChainPolls = 4;
+__device__ uint32_t chain_join(const ChainArgs& ch, uint32_t grid, uint32_t max_polls, uint32_t& n) {
+  uint32_t *s_xcc = ch.sync, *s_mem = ch.sync + 32, *s_arr = ch.sync + 64, *s_n = ch.sync + 96;
+  const uint32_t mine = xcc_id() + 1, first = atomicCAS(s_xcc, 0u, mine);
+  uint32_t rank = kNoItem;
+  if (first == 0 || first == mine) {
+    const uint32_t m = atomicAdd(s_mem, 1u);
+    if (!(m & kClosed)) rank = m;
+  }
+  atomicAdd(s_arr, 1u);
+  if (rank == kNoItem) return kNoItem;
+  if (rank == 0) {
+    for (uint32_t idle = 0; idle < kDoorPolls && coherent_u32(s_arr) < grid; idle++) __builtin_amdgcn_s_sleep(1);
+    n = atomicOr(s_mem, kClosed);
+    atomicExch(s_n, n);
+    return 0;
+  }
+  for (uint32_t idle = 0; (n = coherent_u32(s_n)) == 0; idle++) {
+    if (idle > kChainPolls * max_polls) return kNoItem;  // member 0 always closes: not reached
+    __builtin_amdgcn_s_sleep(1);
+  }
+  return rank;
+}
+
+// The levels [lv_lo, lv_hi), whose blocks k_prep recorded (at most
+// kChainBlocks blocks and levels).  A step is one tile of every block of a
+// level (a tile reads the tiles before it); its records are dealt over the
+// members' threads.
+__global__ __launch_bounds__(kChainThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_chain(
+    DecodeArgs a, ChainArgs ch, uint32_t lv_lo, uint32_t lv_hi) {
+  __shared__ ExpandSmem<kChainThreads> sm;  // for blocks without records
+  // per block: tiles (kUnprepared: none recorded), then where each tile's records end
+  __shared__ uint16_t s_ends[kChainBlocks][kChainEnds];
+  __shared__ uint32_t s_lv[kChainBlocks + 1];
+  __shared__ uint32_t sh_rank, sh_members, sh_give_up;
+  const uint32_t tid = threadIdx.x;
+  if (tid == 0) {
+    uint32_t n = 0;
+    sh_rank = chain_join(ch, gridDim.x, a.max_polls, n);
+    sh_members = n;
+  }
+  __syncthreads();
+  const uint32_t rank = sh_rank, members = sh_members;
+  if (rank == kNoItem) return;
+  const uint32_t p0 = a.lvl_dev[lv_lo], n_lv = lv_hi - lv_lo, n_blk = a.lvl_dev[lv_hi] - p0;
+  const uint4* recs = reinterpret_cast<const uint4*>(ch.recs);
+  for (uint32_t l = tid; l <= n_lv; l += kChainThreads) s_lv[l] = a.lvl_dev[lv_lo + l] - p0;
+  for (uint32_t j = tid; j < n_blk * kChainEnds; j += kChainThreads)
+    s_ends[j / kChainEnds][j % kChainEnds] = (uint16_t)ch.ends[j];
+  __syncthreads();
+  // tile t of block b: its first record, and how many there are
+  auto tile_of = [&](uint32_t b, uint32_t t, uint32_t& r0) -> uint32_t {
+    const uint32_t tiles = s_ends[b][0];
+    if (tiles == kUnprepared || t >= tiles) return 0;
+    r0 = t ? s_ends[b][t] : 0u;
+    return s_ends[b][t + 1] - r0;
+  };
+  struct Step {
+    uint32_t l, t, n, tiles;  // level, tile; records of the step; tiles of the level's blocks, at most
+  };
+  auto open_step = [&](uint32_t l, uint32_t t) {
+    Step s{l, t, 0, 1};
+    if (l >= n_lv) return s;
+    for (uint32_t b = s_lv[l]; b < s_lv[l + 1]; b++) {
+      uint32_t r0 = 0;
+      s.n += tile_of(b, t, r0);
+      const uint32_t tiles = s_ends[b][0];
+      if (tiles != kUnprepared && tiles > s.tiles) s.tiles = tiles;
+    }
+    return s;
+  };
+  // records q0 + (j * members + rank) * kChainThreads + tid of the step,
+  // numbered through its blocks: the record, and a bit for whether there is one
+  uint4 cur[kChainPer], nxt[kChainPer];
+  const uint32_t lane0 = rank * kChainThreads + tid, stride = members * kChainThreads, batch = kChainPer * stride;
+  auto fetch = [&](const Step& s, uint32_t q0, uint4(&r)[kChainPer]) -> uint32_t {
+    uint32_t on = 0, rem = q0 + lane0, b = 0, hi = 0;
+    if (s.l < n_lv) {
+      b = s_lv[s.l];
+      hi = s_lv[s.l + 1];
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < kChainPer; j++) {
+      uint32_t r0 = 0;
+      for (uint32_t n; b < hi && rem >= (n = tile_of(b, s.t, r0)); b++) rem -= n;
+      r[j] = make_uint4(0, 0, 0, 0);
+      if (b < hi) {
+        const u32x4 v = *gp(reinterpret_cast<const u32x4*>(recs + (uint64_t)b * ch.rec_cap + r0 + rem));
+        r[j] = make_uint4(v.x, v.y, v.z, v.w);
+        on |= 1u << j;
+      }
+      rem += stride;
+    }
+    return on;
+  };
+  Step s = open_step(0, 0);
+  uint32_t q0 = 0, done = 0;
+  bool give_up = false;
+  unsigned long long c0 = a.trace ? (unsigned long long)wall_clock64() : 0ull;
+  uint32_t on = fetch(s, 0, cur);
+  while (s.l < n_lv) {
+    uint4 v[kChainPer];
+#pragma unroll
+    for (uint32_t j = 0; j < kChainPer; j++) v[j] = rec_load(cur[j], (on >> j) & 1);
+    // the records that follow: of this step, or the next one's first
+    const bool end = q0 + batch >= s.n;
+    Step sn = s;
+    uint32_t qn = q0 + batch;
+    if (end) {
+      sn = s.t + 1 < s.tiles ? open_step(s.l, s.t + 1) : open_step(s.l + 1, 0);
+      qn = 0;
+    }
+    const uint32_t on_n = fetch(sn, qn, nxt);
+#pragma unroll
+    for (uint32_t j = 0; j < kChainPer; j++)
+      if ((on >> j) & 1) rec_store(cur[j], v[j]);
+    if (end) {
+      if (s.t == 0) {  // blocks without records, one to a member
+        for (uint32_t b = s_lv[s.l] + rank; b < s_lv[s.l + 1]; b += members) {
+          if (s_ends[b][0] != kUnprepared) continue;
+          expand_block<kChainThreads>(a, p0 + b, sm);
+          lds_barrier();
+        }
+      }
+      // hand over: every wave's stores have reached the XCD's L2 before its
+      // member is counted; the members' next loads miss the vector caches
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+      __syncthreads();
+      done += members;
+      if (sn.l < n_lv) {
+        if (tid == 0 && members > 1) {
+          uint32_t seen = l2_add(ch.sync + 128, 1u) + 1;
+          for (uint32_t idle = 0; !give_up && seen < done; idle++) {
+            __builtin_amdgcn_s_sleep(1);
+            const uint32_t now = l2_add(ch.sync + 128, 0u);
+            if (now != seen) idle = 0;
+            seen = now;
+            if (idle > kChainPolls * a.max_polls) {
+              flag(a.err, kErrTimeout);
+              give_up = true;  // no further waits: the launch ends
+            }
+          }
+          sh_give_up = give_up ? 1u : 0u;
+        }
+        // one wave drops the CU's vector cache for all of them
+        if (tid < 64 && members > 1) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        __syncthreads();
+        if (members > 1) give_up = sh_give_up != 0;
+      }
+      if (a.trace && rank == 0 && sn.l != s.l) {
+        const unsigned long long c1 = (unsigned long long)wall_clock64();
+        for (uint32_t b = s_lv[s.l] + tid; b < s_lv[s.l + 1]; b += kChainThreads) {
+          a.trace[8ull * (p0 + b)] = c0;
+          a.trace[8ull * (p0 + b) + 1] = c1;
+        }
+        c0 = c1;
+      }
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < kChainPer; j++) cur[j] = nxt[j];
+    on = on_n;
+    s = sn;
+    q0 = qn;
   }
 }
 
@@ -1718,19 +2078,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kThrea
 // polls); expansions then no longer read earlier blocks, so the launch always
 // drains (its output is then not valid, and ace_check reports the timeout).
 // ---------------------------------------------------------------------------
-// The XCD (accelerator complex die) this wave runs on: the XCC_ID hardware
-// register, bits 3:0.
-__device__ __forceinline__ uint32_t xcc_id() {
-  return __builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 20) & (kMaxXcc - 1);
-}
-
 constexpr uint32_t kPersistThreads = 128;
-constexpr uint32_t kNoItem = 0xffffffffu;
-
-// A counter shared across workgroups, read at agent scope.
-__device__ __forceinline__ uint32_t coherent_u32(const uint32_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 
 // Blocks of a level of `size` blocks in slice r.
 __device__ __forceinline__ uint32_t slice_size(uint32_t size, uint32_t r) {
@@ -2162,6 +2510,19 @@ hipError_t launch_expand_level_dev(const DecodeArgs& a, uint32_t level, uint32_t
   const uint32_t r4 = expand4_resident();
   const uint32_t cap = r4 ? 2 * r4 : kStrideGridExpand;
   return launch_expand(a, width < cap ? width : cap, 0u, (int)level, waves, s);
+}
+
+// k_chain's workgroups: ten members on the XCD that is chosen, when they are
+// dealt over the eight in turn.  More members copy a level sooner and hand it
+// over later.
+constexpr uint32_t kChainGrid = 8 * 10;
+hipError_t launch_chain(const DecodeArgs& a, const ChainArgs& ch, uint32_t lv_lo, uint32_t lv_hi, uint32_t blocks,
+                        hipStream_t s) {
+  if (blocks == 0 || lv_hi <= lv_lo) return hipSuccess;
+  if (blocks > kChainBlocks || lv_hi - lv_lo > kChainBlocks) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_prep, dim3(blocks), dim3(kPrepThreads), 0, s, a, ch, lv_lo, lv_hi);
+  hipLaunchKernelGGL(k_chain, dim3(kChainGrid), dim3(kChainThreads), 0, s, a, ch, lv_lo, lv_hi);
+  return hipGetLastError();
 }
 
 hipError_t launch_batch_mark(const BatchArgs& b, hipStream_t s) {
