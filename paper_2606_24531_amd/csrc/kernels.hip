@@ -674,21 +674,26 @@ constexpr uint32_t kPoison = 1u, kSlow = 2u, kPend = 4u, kExt = 8u;
 constexpr uint32_t kUnres = kPoison | kSlow | kPend;  // flags of a span without an address
 constexpr uint32_t kDepCache = 800;  // dependency lists cached in LDS per block (longer: read from HBM)
 constexpr uint32_t kMaxJumps = 12;   // pointer-doubling rounds (chains up to 4096)
-constexpr uint32_t kPer = 2;         // output pieces per thread per round
 constexpr uint32_t kSlowPer = 8;     // slow bytes per thread per round
 // A tile with more slow bytes per thread than this resolves them in rounds
 // (slow_rounds), one with fewer follows each run back by itself.  A round costs
-// about 7 us however few bytes it holds; walking costs 2 us a tile when there
+// some 5 us however few bytes it holds; walking costs 2 us a tile when there
 // are few and, in the genome blocks that copy regions just written, whose
 // chains are up to ten hops long, 50 (16 KiB) to 150 us (64 KiB), which set
-// the end of their level.  Expansion of 256 MiB mixed at 1, 2 and 4: 354, 354
-// and 354 us (415 without rounds); of 48 MiB in 64 KiB blocks 217, 203 and 203
-// us (302); of 9.9 MB of text in 10,000-byte blocks 91, 94 and 100 us (102).
-constexpr uint32_t kSlowWalk = 2;
+// the end of their level.  Expansion of 256 MiB mixed 341 us at 1 and at 2 (415
+// without rounds); of 48 MiB in 64 KiB blocks 199 and 202 us (302); of 9.9 MB
+// of text in 10,000-byte blocks 88 and 94 us (102); half and a quarter a byte
+// per thread within 1% of 1.
+constexpr uint32_t kSlowWalk = 1;
 
 template <uint32_t kThreads>
 struct ExpandSmem {
   static constexpr uint32_t kSeq = 2 * kThreads;    // sequences per tile (two per thread)
+  // output pieces per thread per round: small launches take 256 threads, where
+  // fewer rounds shorten a block; in large ones more pieces cost a wavefront
+  // per SIMD.  Expansion of 32 MiB FASTQ at 2, 3, 4 and 6 (256 threads): 91,
+  // 89, 93 and 92 us; of 48 MiB in 64 KiB blocks 198, 189, 196 and 189 us.
+  static constexpr uint32_t kPer = kThreads == 256 ? 3 : 2;
   static constexpr uint32_t kRound = kPer * kThreads;  // output pieces per round (kPer per thread)
   static constexpr uint32_t kSlowRound = kSlowPer * kThreads;  // slow bytes resolved at a time
   union {
@@ -1037,7 +1042,9 @@ __device__ __forceinline__ uint32_t slow_rounds(const DecodeArgs& a, ExpandSmem<
   lds_barrier();  // the pieces' tables are dead from here
   for (uint32_t u0 = 0; u0 < n_slow; u0 += kR) {
     uint32_t e[kSlowPer], pos[kSlowPer];
-    const uint32_t ub = u0 + kSlowPer * tid, un = ub < n_slow ? min(kSlowPer, n_slow - ub) : 0u;
+    // a thread takes as few bytes as there are threads for
+    const uint32_t left = n_slow - u0, per = left >= kR ? kSlowPer : (left + kThreads - 1) / kThreads;
+    const uint32_t ub = u0 + per * tid, un = ub < n_slow ? min(per, n_slow - ub) : 0u;
     uint32_t k = un ? slow_slot<kThreads>(sm, c, ub) : 0u;
 #pragma unroll
     for (uint32_t j = 0; j < kSlowPer; j++) e[j] = pos[j] = 0;
@@ -1091,7 +1098,7 @@ __device__ __forceinline__ uint32_t slow_rounds(const DecodeArgs& a, ExpandSmem<
     bool pend = false;
 #pragma unroll
     for (uint32_t j = 0; j < kSlowPer; j++) {
-      sm.par[kSlowPer * tid + j] = e[j];
+      if (j < un) sm.par[(per * tid + j) % kR] = e[j];
       pend = pend || (e[j] & kFromSlow);
     }
     lds_barrier();
@@ -1101,7 +1108,7 @@ __device__ __forceinline__ uint32_t slow_rounds(const DecodeArgs& a, ExpandSmem<
       for (uint32_t j = 0; j < kSlowPer; j++) {
         if (!(e[j] & kFromSlow)) continue;
         e[j] = sm.par[(e[j] & kFromMask) % kR];
-        sm.par[kSlowPer * tid + j] = e[j];
+        sm.par[(per * tid + j) % kR] = e[j];
         pend = pend || (e[j] & kFromSlow);
       }
     }
@@ -1110,7 +1117,7 @@ __device__ __forceinline__ uint32_t slow_rounds(const DecodeArgs& a, ExpandSmem<
 #pragma unroll
     for (uint32_t j = 0; j < kSlowPer; j++) {
       v[j] = 0;
-      if (ub + j >= n_slow) continue;
+      if (j >= un) continue;
       const uint8_t* q = c.out + (e[j] & kFromMask);
       if (e[j] & kFromBlock) q = slow_ext_addr<kThreads>(a, sm, c, e[j] & kFromMask);
       if (q) v[j] = ld8(q);
@@ -1118,7 +1125,7 @@ __device__ __forceinline__ uint32_t slow_rounds(const DecodeArgs& a, ExpandSmem<
 #pragma unroll
     for (uint32_t j = 0; j < kSlowPer; j++) {
       const uint32_t u = ub + j;
-      if (u >= n_slow) continue;
+      if (j >= un) continue;
       st8(c.out + pos[j], v[j]);
       if (e[j] & (kFromExt | kFromBlock)) {
         n_ext++;
@@ -1289,6 +1296,7 @@ template <uint32_t kThreads, bool kPrep = false>
 __device__ __forceinline__ void expand_block(const DecodeArgs& a, uint32_t i, ExpandSmem<kThreads>& sm,
                                              bool ext_ok = true, const PrepOut* po = nullptr) {
   constexpr uint32_t kSeq = ExpandSmem<kThreads>::kSeq, kRound = ExpandSmem<kThreads>::kRound;
+  constexpr uint32_t kPer = ExpandSmem<kThreads>::kPer;
   const uint32_t tid = threadIdx.x;
   const PlanEntry pe = a.plan[i];
   const uint32_t b = pe.block;
@@ -1533,7 +1541,8 @@ __device__ __forceinline__ void expand_block(const DecodeArgs& a, uint32_t i, Ex
       lds_barrier();
     }
     // ---- pieces, kPer per thread per round: thread t takes pieces
-    // t + j * kThreads of the round.  Each sequence marks its first piece;
+    // t + j * kThreads of the round (a round's marks are written after the
+    // last round's scan, whose barrier follows every read of the marks before).  Each sequence marks its first piece;
     // a running maximum over the round's pieces gives every piece its
     // sequence.  All of a thread's loads are issued before any is stored.
     uint32_t carry = 0;  // the last sequence marked in earlier rounds
@@ -1658,7 +1667,6 @@ __device__ __forceinline__ void expand_block(const DecodeArgs& a, uint32_t i, Ex
         }
         store_bytes(c.out + dsto[j], w, len[j]);
       }
-      lds_barrier();  // the marks of the next round are written after every read of this one
     }
     // ---- slow pass: the match bytes of slow sequences (spans that straddle
     // sequences, tiles or non-adjacent blocks), each thread an equal share of
