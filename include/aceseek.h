@@ -253,7 +253,7 @@ int ace_check(void* d_ws, void* stream);
  * a gather of every request to its output offset.  Capacity is fixed at creation; counts are read on the device, so
  * any batch up to the capacity replays the same graph.  The workspace must
  * stay dedicated to the context.  Runs are asynchronous on the stream; a run
- * waits for the previous run of the same context to have started reading its
+ * waits for the previous run of the same context to have read its
  * descriptors.  Errors are read with ace_check(d_ws, stream). */
 typedef struct ace_batch ace_batch;
 int ace_batch_workspace_bytes(const ace_archive* a, uint32_t max_requests, uint64_t* bytes);

@@ -335,20 +335,29 @@ class Archive:
         torch = self._torch
         if out is None:
             out = torch.empty(max(hi - lo, 0), dtype=torch.uint8, device=self.device)
-        host_need = self.workspace_bytes([lo, hi]) if hi > lo else 256
-        if plan == "device":
-            if self.d_plan is None:
-                raise AceError(E_ARG, "device planning needs the resident plan")
-            need = self.seek_device_bytes()
+        if plan == "device" and self.d_plan is None:
+            raise AceError(E_ARG, "device planning needs the resident plan")
+        have = self._ws if ws is None else ws
+        on_device = False
+        if self.d_plan is not None and plan != "host":
+            dev_need = self.seek_device_bytes()
+            on_device = hi > lo and have is not None and have.numel() >= dev_need
+        if on_device:  # planned on the device: no closure walk here
+            ws = have
+            cap = ws.numel()
+        elif plan == "device":
+            if ws is None:
+                ws = self.workspace(dev_need)
+            cap = ws.numel()
+            if cap < dev_need:
+                raise AceError(E_NOSPACE, "device planning needs a %d-byte workspace" % dev_need)
         else:
-            need = host_need
-        if ws is None:
-            ws = self.workspace(need)
-        cap = ws.numel()
-        if plan == "host":
-            cap = min(cap, host_need)
-        elif plan == "device" and cap < need:
-            raise AceError(E_NOSPACE, "device planning needs a %d-byte workspace" % need)
+            host_need = self.workspace_bytes([lo, hi]) if hi > lo else 256
+            if ws is None:
+                ws = self.workspace(host_need)
+            cap = ws.numel()
+            if plan == "host":
+                cap = min(cap, host_need)
         _check(lib().ace_seek(self._h, lo, hi, C.c_void_p(out.data_ptr()),
                               C.c_void_p(ws.data_ptr()), cap, self._tuning(tuning),
                               _stream_ptr(stream)))

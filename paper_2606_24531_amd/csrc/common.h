@@ -113,18 +113,18 @@ struct BatchArgs {
   const uint8_t* arch;
   uint32_t B, n_blocks, depth, cap;
   uint64_t n_total;
-  const uint32_t* order;   // all blocks by level (static)
-  const uint32_t* lstart;  // level boundaries in `order` (depth + 1, static)
+  const uint32_t* lstart;  // level boundaries in `all` (depth + 1, static)
   uint8_t* need;           // per block: needed by this batch
-  uint32_t* pre;           // per position in `order`: needed blocks before it
+  uint32_t* pre;           // per position in `all`: needed blocks before it
   const uint64_t* desc;
   PlanEntry* plan;
   uint32_t* n_plan_dev;
   uint32_t* lvl_dev;       // depth + 1 plan boundaries per level
   uint64_t* loc;
-  const uint8_t* pin;        // per block: 1 = decoded once and kept (its loc stays valid)
-  const uint32_t* pin_base;  // slots taken by kept blocks; planned blocks go after them
-  uint32_t* chunk_cnt;       // compaction: per chunk of `order`, needed blocks (then their prefix)
+  const uint8_t* pin;        // per block: 1 = decoded once and kept (its loc stays valid); null: none kept
+  const uint32_t* pin_base;  // slots taken by kept blocks; planned blocks go after them (null: none)
+  const PlanEntry* all;      // the whole-archive plan's entries: all blocks by level (static)
+  uint32_t* chunk_cnt;       // compaction: per chunk of `all`, needed blocks (then their prefix)
   uint32_t* chunk_seq;       // and their sequences; batch_compact_chunks + 1 entries each
 };
 
@@ -176,9 +176,10 @@ hipError_t launch_batch_compact(const BatchArgs& b, hipStream_t s);
 uint32_t batch_compact_chunks(uint32_t n_blocks);
 // max_len: the longest request (0: not known when launched)
 hipError_t launch_batch_gather(const BatchArgs& b, const DecodeArgs& a, uint64_t max_len, hipStream_t s);
-// a one-request descriptor (n = 1, d_out, then lo, hi at output offset 0)
-// written by a kernel from its arguments
-hipError_t launch_put_range(uint64_t* desc, uint64_t d_out, uint64_t lo, uint64_t hi, hipStream_t s);
+// a one-request descriptor (n = 1, d_out, then lo, hi at output offset 0) and
+// its target blocks marked, the others cleared
+hipError_t launch_seek_init(const BatchArgs& b, uint64_t* desc, uint64_t d_out, uint64_t lo, uint64_t hi,
+                            hipStream_t s);
 hipError_t launch_rans_dev(const DecodeArgs& a, uint32_t cap, uint32_t per_wave, hipStream_t s);
 // entropy decode of levels [lv_lo, lv_hi), whose plan range is read from
 // lvl_dev; width = the most entries those levels can hold

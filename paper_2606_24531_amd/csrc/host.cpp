@@ -1083,7 +1083,7 @@ struct ace_batch {
   uint64_t* staging = nullptr;  // pinned host copy of the descriptors
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
-  hipEvent_t done = nullptr;
+  hipEvent_t done = nullptr, copied = nullptr;  // the last run; its descriptors read from staging
   bool pending = false;
   hipStream_t s2 = nullptr;     // the entropy branch of the captured graph
   std::vector<hipEvent_t> ev;   // fork + one per level (capture edges only)
@@ -1095,8 +1095,8 @@ struct ace_batch {
 
 namespace {
 struct BatchLayout {
-  uint64_t order, lstart, need, pre, plan, nplan, lvl, loc, lit, lens, offs, slots, desc, pin, pinbase,
-      chunks, base, ends, sync, recs, total;
+  uint64_t lstart, need, pre, plan, nplan, lvl, loc, lit, lens, offs, slots, desc, pin, pinbase,
+      chunks, all, base, ends, sync, recs, total;
 };
 
 BatchLayout batch_layout(const ace_archive* A, uint32_t cap) {
@@ -1107,7 +1107,6 @@ BatchLayout batch_layout(const ace_archive* A, uint32_t cap) {
     o = align_up(o + bytes, 256);
     return at;
   };
-  L.order = take(4ull * A->nb);
   L.lstart = take(4ull * (A->depth + 1));
   L.need = take(align_up(A->nb, 4));
   L.pre = take(4ull * A->nb);
@@ -1123,6 +1122,7 @@ BatchLayout batch_layout(const ace_archive* A, uint32_t cap) {
   L.pin = take(align_up(A->nb, 4));
   L.pinbase = take(4);
   L.chunks = take(8ull * (batch_compact_chunks(A->nb) + 1));
+  L.all = take(sizeof(PlanEntry) * A->nb);
   layout_records(A, A->nb, L, o);
   return L;
 }
@@ -1169,7 +1169,6 @@ static int seek_device(const ace_archive* A, uint64_t lo, uint64_t hi, uint8_t* 
   ba.depth = A->depth;
   ba.cap = 1;
   ba.n_total = A->n;
-  ba.order = A->d_order;
   ba.lstart = A->d_lstart;
   ba.need = ws + L.need;
   ba.pre = reinterpret_cast<uint32_t*>(ws + L.pre);
@@ -1178,8 +1177,7 @@ static int seek_device(const ace_archive* A, uint64_t lo, uint64_t hi, uint8_t* 
   ba.n_plan_dev = reinterpret_cast<uint32_t*>(ws + L.nplan);
   ba.lvl_dev = reinterpret_cast<uint32_t*>(ws + L.lvl);
   ba.loc = reinterpret_cast<uint64_t*>(ws + L.loc);
-  ba.pin = ws + L.pin;
-  ba.pin_base = reinterpret_cast<const uint32_t*>(ws + L.pinbase);
+  ba.all = A->d_plan;
   ba.chunk_cnt = reinterpret_cast<uint32_t*>(ws + L.chunks);
   ba.chunk_seq = ba.chunk_cnt + batch_compact_chunks(A->nb) + 1;
   DecodeArgs a{};
@@ -1222,13 +1220,9 @@ static int seek_device(const ace_archive* A, uint64_t lo, uint64_t hi, uint8_t* 
     HIP_TRY(timer_pair(T.ent, 0));
     HIP_TRY(timer_pair(T.mat, 0));
   }
-  // request descriptor, marks and the (empty) kept-block table (the header's
-  // error word and counters accumulate as for every other call)
-  HIP_TRY(launch_put_range(reinterpret_cast<uint64_t*>(ws + L.desc), (uint64_t)(uintptr_t)d_out, lo, hi, s));
-  HIP_TRY(launch_fill_u32(reinterpret_cast<uint32_t*>(ws + L.need), 0u, align_up(A->nb, 4) / 4, s));
-  HIP_TRY(launch_fill_u32(reinterpret_cast<uint32_t*>(ws + L.pin), 0u, align_up(A->nb, 4) / 4, s));
-  HIP_TRY(launch_fill_u32(reinterpret_cast<uint32_t*>(ws + L.pinbase), 0u, 1, s));
-  HIP_TRY(launch_batch_mark(ba, s));
+  // request descriptor and marks (the header's error word and counters
+  // accumulate as for every other call)
+  HIP_TRY(launch_seek_init(ba, reinterpret_cast<uint64_t*>(ws + L.desc), (uint64_t)(uintptr_t)d_out, lo, hi, s));
   for (uint32_t l = A->depth; l-- > 1;)
     HIP_TRY(launch_batch_close(ba, l, A->all_levels[l + 1] - A->all_levels[l], s));
   HIP_TRY(launch_batch_compact(ba, s));
@@ -1284,6 +1278,7 @@ extern "C" void ace_batch_destroy(ace_batch* b) {
   if (b->exec) (void)hipGraphExecDestroy(b->exec);
   if (b->graph) (void)hipGraphDestroy(b->graph);
   if (b->done) (void)hipEventDestroy(b->done);
+  if (b->copied) (void)hipEventDestroy(b->copied);
   for (hipEvent_t e : b->ev) (void)hipEventDestroy(e);
   if (b->s2) (void)hipStreamDestroy(b->s2);
   if (b->staging) (void)hipHostFree(b->staging);
@@ -1308,19 +1303,18 @@ extern "C" int ace_batch_create(const ace_archive* A, uint32_t cap, void* d_ws, 
   int rc = ACE_OK;
   do {
     if (hipHostMalloc((void**)&b->staging, 16 + 24ull * cap, hipHostMallocDefault) != hipSuccess ||
-        hipEventCreateWithFlags(&b->done, hipEventDisableTiming) != hipSuccess) {
+        hipEventCreateWithFlags(&b->done, hipEventDisableTiming) != hipSuccess ||
+        hipEventCreateWithFlags(&b->copied, hipEventDisableTiming) != hipSuccess) {
       rc = fail(ACE_E_HIP, "pinned staging or event allocation failed");
       break;
     }
-    // static planning data: all blocks by level, and the level boundaries
-    std::vector<uint32_t> order(A->nb);
-    for (uint32_t i = 0; i < A->nb; i++) order[i] = A->all_plan[i].block;
-    uint32_t widest = 0;
-    for (uint32_t l = 0; l < A->depth; l++)
-      widest = std::max(widest, A->all_levels[l + 1] - A->all_levels[l]);
-    if (hipMemcpyAsync(b->ws + L.order, order.data(), 4ull * A->nb, hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(b->ws + L.lstart, A->all_levels.data(), 4ull * (A->depth + 1),
+    // static planning data: all blocks by level with their index fields, and
+    // the level boundaries (a copy of its own: the resident plan may be
+    // attached elsewhere while the context lives)
+    if (hipMemcpyAsync(b->ws + L.lstart, A->all_levels.data(), 4ull * (A->depth + 1),
                        hipMemcpyHostToDevice, s) != hipSuccess ||
+        hipMemcpyAsync(b->ws + L.all, A->all_plan.data(), sizeof(PlanEntry) * A->nb, hipMemcpyHostToDevice, s) !=
+            hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess) {
       rc = fail(ACE_E_HIP, "upload of the level order failed");
       break;
@@ -1332,7 +1326,6 @@ extern "C" int ace_batch_create(const ace_archive* A, uint32_t cap, void* d_ws, 
     ba.depth = A->depth;
     ba.cap = cap;
     ba.n_total = A->n;
-    ba.order = reinterpret_cast<const uint32_t*>(b->ws + L.order);
     ba.lstart = reinterpret_cast<const uint32_t*>(b->ws + L.lstart);
     ba.need = b->ws + L.need;
     ba.pre = reinterpret_cast<uint32_t*>(b->ws + L.pre);
@@ -1343,6 +1336,7 @@ extern "C" int ace_batch_create(const ace_archive* A, uint32_t cap, void* d_ws, 
     ba.loc = reinterpret_cast<uint64_t*>(b->ws + L.loc);
     ba.pin = b->ws + L.pin;
     ba.pin_base = reinterpret_cast<const uint32_t*>(b->ws + L.pinbase);
+    ba.all = reinterpret_cast<const PlanEntry*>(b->ws + L.all);
     ba.chunk_cnt = reinterpret_cast<uint32_t*>(b->ws + L.chunks);
     ba.chunk_seq = ba.chunk_cnt + batch_compact_chunks(A->nb) + 1;
     b->off_plan = L.plan;
@@ -1449,7 +1443,6 @@ extern "C" int ace_batch_create(const ace_archive* A, uint32_t cap, void* d_ws, 
       rc = fail(ACE_E_HIP, "graph instantiation failed");
       break;
     }
-    (void)widest;
   } while (0);
   if (rc) {
     ace_batch_destroy(b);
@@ -1509,8 +1502,9 @@ extern "C" int ace_batch_run(ace_batch* b, const ace_range* r, uint32_t n, uint8
     if (r[i].lo > r[i].hi) return fail(ACE_E_ARG, "range %u is inverted", i);
     if (r[i].hi > b->A->n) return fail(ACE_E_RANGE, "range %u ends beyond %llu", i, (unsigned long long)b->A->n);
   }
-  // the staging buffer is reused: the previous replay must have read it
-  if (b->pending) HIP_TRY(hipEventSynchronize(b->done));
+  // the staging buffer is reused: the previous run's copy must have read it
+  // (its replay may still run: this run's copy is behind it on the stream)
+  if (b->pending) HIP_TRY(hipEventSynchronize(b->copied));
   b->staging[0] = n;
   b->staging[1] = (uint64_t)(uintptr_t)d_out;
   for (uint32_t i = 0; i < n; i++) {
@@ -1519,6 +1513,7 @@ extern "C" int ace_batch_run(ace_batch* b, const ace_range* r, uint32_t n, uint8
     b->staging[4 + 3 * i] = out_off[i];
   }
   HIP_TRY(hipMemcpyAsync(b->ws + b->off_desc, b->staging, 16 + 24ull * n, hipMemcpyHostToDevice, b->stream));
+  HIP_TRY(hipEventRecord(b->copied, b->stream));
   HIP_TRY(hipGraphLaunch(b->exec, b->stream));
   HIP_TRY(hipEventRecord(b->done, b->stream));
   b->pending = true;
