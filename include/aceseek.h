@@ -94,10 +94,10 @@ typedef struct {
  *                   blocks)
  *  mode             0 and 1: one entropy launch for every planned block,
  *                   then one match-expansion launch per dependency level,
- *                   all on the caller's stream (with waves_per_block 0, runs
- *                   of small levels, as archives without a level cap have,
- *                   take two launches together: copy records made for all
- *                   of a run's blocks, then copied level after level; the
+ *                   all on the caller's stream (with waves_per_block 0,
+ *                   groups of levels of few blocks are turned into copy
+ *                   records by one launch and then copied level by level,
+ *                   long runs of small levels within one launch; the
  *                   workspace sizes below include the records); 2: one entropy launch,
  *                   then one persistent launch that expands every level in
  *                   turn, synchronised by counters in the workspace (every

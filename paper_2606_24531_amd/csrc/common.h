@@ -79,13 +79,14 @@ struct DecodeArgs {
 // Copy records of a run of small levels (k_prep, k_chain): rec_cap records of
 // 16 bytes per block from recs on, kChainEnds words per block from ends on,
 // and k_chain's counters, one per 128-byte line.
-constexpr uint32_t kChainEnds = 8, kChainBlocks = 1536, kChainSync = 160;
+constexpr uint32_t kChainEnds = 8, kChainBlocks = 1536, kChainSync = 160, kChainRuns = 8;
 constexpr uint32_t kMaxRecs = 65535;  // per block: k_chain holds the counts in 16 bits
 struct ChainArgs {
   uint8_t* recs;
   uint32_t* ends;
-  uint32_t* sync;
+  uint32_t* sync;    // kChainRuns times kChainSync words
   uint32_t rec_cap;
+  uint32_t lv_base;  // the first recorded level: its first block has slot 0
 };
 
 // Entropy coding of token streams on the device (the encoder's rANS step):
@@ -158,10 +159,15 @@ inline void persist_sync(DecodeArgs& a, uint32_t* words) {
   a.lvl_xcd = reinterpret_cast<unsigned long long*>(a.lvl_seen + (uint64_t)kPersistReplicas * kPersistLine);
 }
 hipError_t launch_persistent(const DecodeArgs& a, uint32_t grid, hipStream_t s);
-// levels [lv_lo, lv_hi) (bounds in a.lvl_dev), of at most `blocks` blocks in
-// all, recorded and then copied level by level within one launch
+// Levels (bounds in a.lvl_dev) of at most `blocks` blocks in all: recorded;
+// one recorded level copied; recorded levels copied level by level within one
+// launch (the run-th such launch since they were recorded).
+// exact: `blocks` is their number, not a bound.
+hipError_t launch_prep(const DecodeArgs& a, const ChainArgs& ch, uint32_t lv_lo, uint32_t lv_hi, uint32_t blocks,
+                       bool exact, bool big_tiles, hipStream_t s);
+hipError_t launch_copy_level(const DecodeArgs& a, const ChainArgs& ch, uint32_t level, uint32_t blocks, hipStream_t s);
 hipError_t launch_chain(const DecodeArgs& a, const ChainArgs& ch, uint32_t lv_lo, uint32_t lv_hi, uint32_t blocks,
-                        hipStream_t s);
+                        uint32_t run, hipStream_t s);
 hipError_t launch_copy(const DecodeArgs& a, const CopyItem* items, uint32_t n_items,
                        hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, uint64_t n, hipStream_t s);

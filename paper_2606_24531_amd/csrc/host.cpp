@@ -71,9 +71,10 @@ struct ace_archive {
   std::vector<PlanEntry> all_plan;
   std::vector<uint32_t> all_levels;
   uint64_t all_seq = 0;
-  // copy records of chained levels: per block, and the blocks recorded at a
-  // time (0: the archive has no run of small levels worth it)
-  uint32_t rec_cap = 0, chain_blocks = 0;
+  // copy records: per block; the blocks of a host-planned call recorded at a
+  // time, at most; the same for the whole archive, and for device-planned calls
+  // (0: no group of the archive's levels is recorded)
+  uint32_t rec_cap = 0, rec_blocks = 0, rec_all = 0, rec_dev = 0;
   PlanEntry* all_plan_pinned = nullptr;
   const PlanEntry* d_plan = nullptr;  // the whole-archive plan resident on the device, if attached
   const uint32_t* d_order = nullptr;  // with it: all blocks by level, then the level boundaries
@@ -225,34 +226,65 @@ static void level_order(const ace_archive* A, const std::vector<uint32_t>& block
   }
 }
 
-// Runs of small dependency levels are copied within one launch, from records
-// made ahead (launch_chain).  A level of up to kChainWidth blocks is small: the
-// chain copies 32 blocks of 16 KiB in about the 10 to 16 us that a launch of
-// its own takes a level whatever its size (a seek with three levels of 13 to
-// 20 blocks among 65: 500 us with a width of 12, 450 with 32, 450 with 100).  A
-// run of fewer than kChainRun levels does not pay for its two launches.
-constexpr uint32_t kChainWidth = 32, kChainRun = 3;
-constexpr uint64_t kChainBytes = 64ull << 20;  // records held at a time, at most
+// Of a block's expansion only the copies need the levels below it.  Groups of
+// consecutive levels that hold few blocks together are turned into copy records
+// by one launch (launch_prep), then copied: a level by a launch of its own
+// (launch_copy_level), runs of levels of up to kChainWidth blocks within one
+// launch (launch_chain).  A level's own expansion takes 10 to 28 us whatever its
+// size while its blocks are fewer than the device holds; recording a group takes
+// 15 to 50 us, copying a level 5 to 6 us (12 for 1,000 blocks), and 3.5 us within
+// a chain (which copies 32 blocks of 16 KiB in the time of a launch).  So a group
+// needs kChainRun levels to pay (one more where blocks are larger than
+// kRecBlockSize, whose records take longer: 64 KiB blocks in three levels 207
+// against 189 us), and kRecBlocks blocks at most, as records are memory traffic
+// that a large level does not get back; where the device plans and only the
+// archive's level sizes are known, which a seek's plan seldom reaches,
+// kRecBlocksDev.  Expansion with a launch per level and with groups of up to
+// 1,000, 2,048 and 3,000 blocks: 32 MiB FASTQ (2,048 blocks, of which 960 in the
+// first four levels) 90, 72, 75, 75 us (whole decodes at 1,536 and 2,048: 129 and
+// 136); 9.9 MB of text (988) 88, 62, 62, 62; a range of 1,000 blocks of 2,048 116,
+// 124, 95, 94; 256 MiB mixed 339, 340, 340, 345.  A seek with three levels of 13
+// to 20 blocks among 65 took 500 us with a chain width of 12 and 450 with 32 and
+// 100.
+constexpr uint32_t kChainWidth = 32, kChainRun = 3, kRecBlocks = 1536, kRecBlocksDev = 2048, kRecBlockSize = 32768;
+constexpr uint64_t kRecBytes = 128ull << 20;  // records held at a time, at most
 
-// Consecutive levels that are expanded together: one level by its own launch,
-// or a chained run of at most max_blocks blocks.
+// What a launch does with levels [lo, hi).
+enum class LevelOp { expand, record, copy, chain };
 struct LevelRun {
+  LevelOp op;
   uint32_t lo, hi;
-  bool chain;
+  uint32_t arg;  // record: 1 when a chain follows; chain: which one of its group
 };
-static std::vector<LevelRun> level_runs(const std::vector<uint32_t>& lstart, uint32_t max_blocks) {
+static std::vector<LevelRun> level_runs(const std::vector<uint32_t>& lstart, uint32_t max_blocks, uint32_t B) {
   std::vector<LevelRun> runs;
   uint32_t nl = lstart.empty() ? 0u : (uint32_t)lstart.size() - 1;
   while (nl && lstart[nl] == lstart[nl - 1]) nl--;  // a plan's closure may end below the archive's last level
+  auto size = [&](uint32_t lo, uint32_t hi) { return lstart[hi] - lstart[lo]; };
   for (uint32_t l = 0; l < nl;) {
     uint32_t e = l;
-    while (e < nl && lstart[e + 1] - lstart[e] <= kChainWidth && lstart[e + 1] - lstart[l] <= max_blocks &&
-           e + 1 - l <= max_blocks)
-      e++;
-    const bool chain = e - l >= kChainRun;
-    if (!chain) e = l + 1;
-    runs.push_back(LevelRun{l, e, chain});
-    l = e;
+    while (e < nl && size(l, e + 1) <= max_blocks) e++;
+    if (e - l < (B <= kRecBlockSize ? kChainRun : kChainRun + 1)) {
+      runs.push_back(LevelRun{LevelOp::expand, l, l + 1, 0});
+      l++;
+      continue;
+    }
+    const size_t rec = runs.size();
+    runs.push_back(LevelRun{LevelOp::record, l, e, 0});
+    for (uint32_t chains = 0; l < e;) {
+      uint32_t c = l;
+      while (c < e && chains < kChainRuns && size(c, c + 1) <= kChainWidth && size(l, c + 1) <= kChainBlocks &&
+             c + 1 - l <= kChainBlocks)
+        c++;
+      if (c - l >= kChainRun) {
+        runs.push_back(LevelRun{LevelOp::chain, l, c, chains++});
+        runs[rec].arg = 1;
+        l = c;
+      } else {
+        runs.push_back(LevelRun{LevelOp::copy, l, l + 1, 0});
+        l++;
+      }
+    }
   }
   return runs;
 }
@@ -287,10 +319,13 @@ extern "C" int ace_archive_open(const uint8_t* h_arch, uint64_t len, const void*
   // some for its runs of straddling bytes (a block that needs more is expanded
   // without records)
   A->rec_cap = A->B / 8 + 512;
-  uint32_t fit = (uint32_t)std::min<uint64_t>(kChainBlocks, kChainBytes / (16ull * A->rec_cap));
-  if (A->rec_cap > kMaxRecs) fit = 0;
-  for (const LevelRun& r : level_runs(A->all_levels, fit))
-    if (r.chain) A->chain_blocks = fit;
+  const uint64_t fit = A->depth >= kChainRun && A->rec_cap <= kMaxRecs ? kRecBytes / (16ull * A->rec_cap) : 0;
+  A->rec_blocks = (uint32_t)std::min<uint64_t>(kRecBlocks, fit);
+  const uint32_t dev = (uint32_t)std::min<uint64_t>(kRecBlocksDev, fit);
+  for (const LevelRun& r : level_runs(A->all_levels, A->rec_blocks, A->B))
+    if (r.op == LevelOp::record) A->rec_all = std::min(A->rec_blocks, A->nb);
+  for (const LevelRun& r : level_runs(A->all_levels, dev, A->B))
+    if (r.op == LevelOp::record) A->rec_dev = std::min(dev, A->nb);
   *out = A;
   return ACE_OK;
 }
@@ -429,13 +464,12 @@ struct Layout {
   uint64_t ends, sync, recs, total;
 };
 
-// The copy records of chained levels, at the end of a workspace.
+// The copy records of nb blocks, at the end of a workspace.
 template <typename L>
-void layout_records(const ace_archive* A, uint64_t n_plan, L& l, uint64_t o) {
-  const uint64_t nb = std::min<uint64_t>(A->chain_blocks, n_plan);
+void layout_records(const ace_archive* A, uint64_t nb, L& l, uint64_t o) {
   l.base = o;
   l.ends = o;  o = align_up(o + 4ull * kChainEnds * nb, 256);
-  l.sync = o;  o = align_up(o + (nb ? 4ull * kChainSync : 0), 256);
+  l.sync = o;  o = align_up(o + (nb ? 4ull * kChainSync * kChainRuns : 0), 256);
   l.recs = o;  o = align_up(o + 16ull * A->rec_cap * nb, 256);
   l.total = o;
 }
@@ -446,14 +480,42 @@ ChainArgs chain_args(const ace_archive* A, const L& l, uint8_t* ws) {
   c.ends = reinterpret_cast<uint32_t*>(ws + l.ends);
   c.sync = reinterpret_cast<uint32_t*>(ws + l.sync);
   c.rec_cap = A->rec_cap;
+  c.lv_base = 0;
   return c;
+}
+
+// The expansion of a plan whose level sizes are (exact) or are bounded by
+// (device-planned) lstart's, as runs says; expand(l) launches one level's own.
+template <typename L, typename F>
+hipError_t run_levels(const ace_archive* A, const DecodeArgs& a, const std::vector<uint32_t>& lstart,
+                      const std::vector<LevelRun>& runs, bool exact, const L& l, uint8_t* ws, hipStream_t s,
+                      F&& expand) {
+  ChainArgs c = chain_args(A, l, ws);
+  hipError_t e = hipSuccess;
+  for (const LevelRun& r : runs) {
+    const uint32_t n = lstart[r.hi] - lstart[r.lo];
+    switch (r.op) {
+      case LevelOp::expand: e = expand(r.lo); break;
+      case LevelOp::record:
+        c.lv_base = r.lo;
+        // a chain hands over after every tile: larger ones, so that a block is one
+        e = launch_prep(a, c, r.lo, r.hi, n, exact, r.arg != 0 || A->B > 16384, s);
+        break;
+      case LevelOp::copy: e = launch_copy_level(a, c, r.lo, n, s); break;
+      case LevelOp::chain: e = launch_chain(a, c, r.lo, r.hi, n, r.arg, s); break;
+    }
+    if (e != hipSuccess) break;
+  }
+  return e;
 }
 
 // Workspace of one host-planned decode.  lv: per dependency level of the
 // archive, the plan's level boundaries (depth + 1), then the persistent
 // kernel's finished counts (depth) and its finished-level copies.
-Layout layout(const ace_archive* A, uint64_t n_plan, uint64_t n_seq, uint64_t n_slots,
-              uint64_t n_items) {
+// Workspace of a plan of n_plan blocks (whole: all of the archive's, in its
+// own level sizes).
+Layout layout(const ace_archive* A, uint64_t n_plan, uint64_t n_seq, uint64_t n_slots, uint64_t n_items,
+              bool whole = false) {
   Layout L;
   uint64_t o = kWsHeader;
   L.plan = o;  o = align_up(o + sizeof(PlanEntry) * n_plan, 256);
@@ -464,7 +526,7 @@ Layout layout(const ace_archive* A, uint64_t n_plan, uint64_t n_seq, uint64_t n_
   L.offs = o;  o = align_up(o + (uint64_t)A->ow * n_seq, 256);
   L.slots = o; o = align_up(o + (uint64_t)A->B * n_slots, 256);
   L.items = o; o = align_up(o + sizeof(CopyItem) * n_items, 256);
-  layout_records(A, n_plan, L, o);
+  layout_records(A, whole ? A->rec_all : std::min<uint64_t>(A->rec_blocks, n_plan), L, o);
   return L;
 }
 
@@ -642,31 +704,29 @@ static int run_launches(const ace_archive* A, const PlanEntry* entries, uint64_t
       for (size_t l = split; l < nl; l++) HIP_TRY(expand(l));
     } else {
       std::vector<LevelRun> runs;
-      if (chain && A->chain_blocks && waves == 0)
-        runs = level_runs(lstart, (uint32_t)std::min<uint64_t>(A->chain_blocks, n_plan));
-      const bool chained = std::any_of(runs.begin(), runs.end(), [](const LevelRun& r) { return r.chain; });
-      if (chained) {  // the kernels read the level boundaries on the device
+      if (chain && waves == 0)
+        runs = level_runs(lstart, resident ? A->rec_all : (uint32_t)std::min<uint64_t>(A->rec_blocks, n_plan), A->B);
+      const bool recorded =
+          std::any_of(runs.begin(), runs.end(), [](const LevelRun& r) { return r.op == LevelOp::record; });
+      if (recorded) {  // the kernels read the level boundaries on the device
         if (resident)
           a.lvl_dev = A->d_lstart;
         else
           HIP_TRY(hipMemcpyAsync(ws + L.lv, lstart.data(), 4ull * lstart.size(), hipMemcpyHostToDevice, s));
       }
       HIP_TRY(entropy(0, (uint32_t)n_plan, s));
-      if (!chained)
+      if (!recorded) {
         for (size_t l = 0; l < nl; l++) HIP_TRY(expand(l));
-      else
-        for (const LevelRun& r : runs) {
-          if (!r.chain) {
-            HIP_TRY(expand(r.lo));
-            continue;
-          }
-          if (timed) {
-            HIP_TRY(timer_pair(T.mat, T.n_mat));
-            HIP_TRY(hipEventRecord(T.mat[2 * T.n_mat], s));
-          }
-          HIP_TRY(launch_chain(a, chain_args(A, L, ws), r.lo, r.hi, lstart[r.hi] - lstart[r.lo], s));
-          if (timed) HIP_TRY(hipEventRecord(T.mat[2 * T.n_mat++ + 1], s));
+      } else {
+        if (timed) {
+          HIP_TRY(timer_pair(T.mat, T.n_mat));
+          HIP_TRY(hipEventRecord(T.mat[2 * T.n_mat], s));
         }
+        HIP_TRY(run_levels(A, a, lstart, runs, true, L, ws, s, [&](uint32_t l) {
+          return launch_expand_level(a, lstart[l], lstart[l + 1], waves, s);
+        }));
+        if (timed) HIP_TRY(hipEventRecord(T.mat[2 * T.n_mat++ + 1], s));
+      }
     }
     T.recorded = timed;
   }
@@ -679,7 +739,7 @@ extern "C" int ace_workspace_bytes(const ace_archive* A, const ace_range* r, uin
                                    uint64_t* bytes) {
   if (!A || !bytes || (n && !r)) return fail(ACE_E_ARG, "null argument");
   if (n == 0) {
-    *bytes = layout(A, A->nb, A->all_seq, 0, 0).total;
+    *bytes = layout(A, A->nb, A->all_seq, 0, 0, true).total;
     return ACE_OK;
   }
   std::vector<uint8_t> need(A->nb, 0);
@@ -710,7 +770,7 @@ extern "C" int ace_decode_all(const ace_archive* A, uint8_t* d_out, uint64_t out
   if (!A || (!d_out && A->n) || !d_ws) return fail(ACE_E_ARG, "null argument");
   if (int rc = need_resident(A)) return rc;
   if (out_cap < A->n) return fail(ACE_E_NOSPACE, "output needs %llu bytes", (unsigned long long)A->n);
-  Layout L = layout(A, A->nb, A->all_seq, 0, 0);
+  Layout L = layout(A, A->nb, A->all_seq, 0, 0, true);
   if (ws_cap < L.total) return fail(ACE_E_NOSPACE, "workspace needs %llu bytes", (unsigned long long)L.total);
   if (A->nb == 0) return ACE_OK;
   if (A->d_plan)
@@ -1123,28 +1183,19 @@ BatchLayout batch_layout(const ace_archive* A, uint32_t cap) {
   L.pinbase = take(4);
   L.chunks = take(8ull * (batch_compact_chunks(A->nb) + 1));
   L.all = take(sizeof(PlanEntry) * A->nb);
-  layout_records(A, A->nb, L, o);
+  layout_records(A, A->rec_dev, L, o);
   return L;
 }
 
-// The expansion launches of a device-planned decode, level by level, runs of
-// small levels chained.
+// The expansion launches of a device-planned decode.
 // Level sizes are read on the device; the archive's bound them.
 hipError_t expand_levels_dev(const ace_archive* A, const DecodeArgs& a, const BatchLayout& L, uint8_t* ws,
                              bool chain, uint32_t waves, hipStream_t s) {
   const std::vector<uint32_t>& lv = A->all_levels;
-  std::vector<LevelRun> runs;
-  if (chain && A->chain_blocks && waves == 0)
-    runs = level_runs(lv, std::min(A->chain_blocks, A->nb));
-  else
-    for (uint32_t l = 0; l < A->depth; l++) runs.push_back(LevelRun{l, l + 1, false});
-  hipError_t e = hipSuccess;
-  for (const LevelRun& r : runs) {
-    e = r.chain ? launch_chain(a, chain_args(A, L, ws), r.lo, r.hi, lv[r.hi] - lv[r.lo], s)
-                : launch_expand_level_dev(a, r.lo, lv[r.hi] - lv[r.lo], waves, s);
-    if (e != hipSuccess) break;
-  }
-  return e;
+  return run_levels(A, a, lv, level_runs(lv, chain && waves == 0 ? A->rec_dev : 0u, A->B), false, L, ws, s,
+                    [&](uint32_t l) {
+    return launch_expand_level_dev(a, l, lv[l + 1] - lv[l], waves, s);
+  });
 }
 }  // namespace
 

@@ -1288,6 +1288,17 @@ struct PrepOut {
   uint32_t* n;  // LDS: records of the block so far
 };
 
+// Writes record `slot` of a block: n (1..16) bytes from q (null: zeros), with
+// win readable bytes around it, to dst.
+__device__ __forceinline__ void put_rec(const PrepOut& po, uint32_t slot, const uint8_t* q, uint32_t win,
+                                        uint8_t* dst, uint32_t n) {
+  if (slot >= po.cap) return;
+  const uint32_t back = win & 31u, fwd = win >> 5, sh = fwd < 16 ? 16 - fwd : 0u;
+  const uint32_t kind = !q ? kZero : sh > back ? kBytes : kCopy;
+  po.rec[slot] = make_rec((uint64_t)(uintptr_t)q - (kind == kCopy ? sh : 0u), (uint64_t)(uintptr_t)dst, n,
+                          kind == kCopy ? sh : 0u, kind, 0, 0);
+}
+
 // Expands plan entry i with kThreads threads.  Sources in earlier blocks must
 // be complete and visible (unless ext_ok is false, after a timed-out wait).
 // kPrep: writes the block's copy records instead of its bytes (reads no
@@ -1694,15 +1705,10 @@ __device__ __forceinline__ void expand_block(const DecodeArgs& a, uint32_t i, Ex
         const uint8_t* q = resolve_run<kThreads>(a, sm, c, k, p, run, ext, win);
         const uint32_t n = min(min(run, u1 - u), end_k - u);
         if (ext) n_ext += n;
-        for (uint32_t i = 0; kPrep && i < n; i += 16) {
-          const uint32_t len = n - i < 16 ? n - i : 16u, slot = atomicAdd(po->n, 1u);
-          const uint32_t back = (win & 31u) + i, fwd = (win >> 5) > i ? (win >> 5) - i : 0u;
-          const uint32_t sh = fwd < 16 ? 16 - fwd : 0u;
-          const uint32_t kind = !q ? kZero : sh > back ? kBytes : kCopy;
-          const uint64_t src = (uint64_t)(uintptr_t)q + i - (kind == kCopy ? sh : 0u);
-          if (slot < po->cap)
-            po->rec[slot] = make_rec(src, (uint64_t)(uintptr_t)(c.out + p + i), len, kind == kCopy ? sh : 0u, kind, 0, 0);
-        }
+        for (uint32_t i = 0; kPrep && i < n; i += 16)
+          put_rec(*po, atomicAdd(po->n, 1u), q ? q + i : q,
+                  win_pack((win & 31u) + i, (win >> 5) > i ? (win >> 5) - i : 0u), c.out + p + i,
+                  n - i < 16 ? n - i : 16u);
         for (uint32_t i = 0; !kPrep && i < n; i += 4) {
           uint8_t v[4];
 #pragma unroll
@@ -1772,19 +1778,23 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kThrea
 }
 
 // ---------------------------------------------------------------------------
-// Chains of small dependency levels.
+// Copy records and chains of small dependency levels.
 //
-// An archive without a level cap has hundreds to thousands of levels of a few
-// blocks.  A launch per level costs each one block's whole latency (token
-// scans, classification, pointer doubling, walks: 8 to 15 us) and a launch.
-// Of that work only the copies need the levels below, so a run of small
-// levels takes two launches: k_prep turns every block of the run into copy
-// records at once, and k_chain copies level after level with a few workgroups
-// of one XCD.  Their stores meet in that XCD's L2, so a level is handed on by
-// a counter in memory without the L2 writeback that workgroups on different
-// XCDs would need.
+// A launch per level costs each level of few blocks one block's whole latency
+// (token scans, classification, pointer doubling, walks: 8 to 25 us) and a
+// launch.  Of that work only the copies need the levels below.  So k_prep turns
+// the blocks of a group of levels into copy records at once, and then
+// k_copy_level copies a level, one workgroup per block; and for the hundreds to
+// thousands of levels of a few blocks that an archive without a level cap has,
+// k_chain copies level after level in one launch, with a few workgroups of one
+// XCD.  Their stores meet in that XCD's L2, so a level is handed on by a counter
+// there without the L2 writeback that workgroups on different XCDs would need.
 //
-// What bounds a level is a load's and a store's latency and the hand-over,
+// k_prep is bounded by its slowest block (the walks of its straddling bytes),
+// k_copy_level by launch and three round trips (5 to 6 us a level; 20 to 28 as
+// expanded).  Expansion of a 4 KB seek 74 -> 59 us, of 9.9 MB of text in four
+// levels 88 -> 62, of 32 MiB FASTQ in five 90 -> 75.
+// What bounds a chain's level is a load's and a store's latency and the hand-over,
 // about 3.5 us (a counter at agent scope instead of in the L2, and every wave
 // dropping the vector cache, made it 6.5 us).  One workgroup alone (no
 // hand-over) is bounded by its CU's address processing, some 340 cycles per
@@ -1794,22 +1804,28 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kThrea
 // levels 3.10 -> 0.69 ms, 1 MiB genome of 27 levels 0.51 -> 0.18 ms, 6 MiB
 // FASTQ 4.05 -> 0.85 ms, 6 MiB text in 64 KiB blocks 6.5 -> 0.82 ms.
 // ---------------------------------------------------------------------------
-constexpr uint32_t kPrepThreads = 512, kChainThreads = 512, kChainPer = 1;
+constexpr uint32_t kChainThreads = 512, kChainPer = 1;
 
-__global__ __launch_bounds__(kPrepThreads) void k_prep(DecodeArgs a, ChainArgs ch, uint32_t lv_lo, uint32_t lv_hi) {
-  __shared__ ExpandSmem<kPrepThreads> sm;
+// Records of the blocks of levels [lv_lo, lv_hi) of the plan, one workgroup
+// each, in slots from 0 on; nothing unless they are more than n_lo and at most
+// n_hi.
+template <uint32_t kThreads>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kThreads == 256 ? 4 : 2))) void k_prep(
+    DecodeArgs a, ChainArgs ch, uint32_t lv_lo, uint32_t lv_hi, uint32_t n_lo, uint32_t n_hi) {
+  __shared__ ExpandSmem<kThreads> sm;
   __shared__ uint32_t n_rec;
-  // the following k_chain's counters
-  if (blockIdx.x == 0 && threadIdx.x < kChainSync) ch.sync[threadIdx.x] = 0;
-  const uint32_t i = a.lvl_dev[lv_lo] + blockIdx.x;
-  if (i >= a.lvl_dev[lv_hi]) return;
+  // the counters of the k_chain launches that follow
+  if (blockIdx.x == 0)
+    for (uint32_t j = threadIdx.x; j < kChainSync * kChainRuns; j += kThreads) ch.sync[j] = 0;
+  const uint32_t i = a.lvl_dev[lv_lo] + blockIdx.x, n = a.lvl_dev[lv_hi] - a.lvl_dev[lv_lo];
+  if (blockIdx.x >= n || n <= n_lo || n > n_hi) return;
   PrepOut po;
   po.rec = reinterpret_cast<uint4*>(ch.recs) + (uint64_t)blockIdx.x * ch.rec_cap;
   po.cap = ch.rec_cap;
   po.ends = ch.ends + (uint64_t)blockIdx.x * kChainEnds;
   po.n = &n_rec;
   if (threadIdx.x == 0) n_rec = 0;
-  expand_block<kPrepThreads, true>(a, i, sm, true, &po);
+  expand_block<kThreads, true>(a, i, sm, true, &po);
 }
 
 // The bytes of record r (see make_rec), to be moved down by its shift; a
@@ -1871,6 +1887,56 @@ __device__ __forceinline__ uint32_t l2_add(uint32_t* p, uint32_t v) {
   return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
+// One level of recorded blocks, one workgroup per block: its records, tile
+// after tile.  The first records are loaded before their number is known
+// (slots hold rec_cap), so a block of one tile is three round trips: record,
+// source, store.
+constexpr uint32_t kCopyThreads = 256, kCopyPer = 6;
+__global__ __launch_bounds__(kCopyThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_copy_level(
+    DecodeArgs a, ChainArgs ch, uint32_t level) {
+  __shared__ ExpandSmem<kCopyThreads> sm;  // for blocks without records
+  const uint32_t tid = threadIdx.x, i = a.lvl_dev[level] + blockIdx.x;
+  if (i >= a.lvl_dev[level + 1]) return;
+  const uint32_t slot = i - a.lvl_dev[ch.lv_base];
+  const unsigned long long c0 = a.trace ? (unsigned long long)wall_clock64() : 0ull;
+  const uint4* recs = reinterpret_cast<const uint4*>(ch.recs) + (uint64_t)slot * ch.rec_cap;
+  const uint32_t* ends = ch.ends + (uint64_t)slot * kChainEnds;
+  auto fetch = [&](uint32_t q) {
+    const u32x4 v = *gp(reinterpret_cast<const u32x4*>(recs + (q < ch.rec_cap ? q : 0u)));
+    return make_uint4(v.x, v.y, v.z, v.w);
+  };
+  uint4 r[kCopyPer];
+#pragma unroll
+  for (uint32_t j = 0; j < kCopyPer; j++) r[j] = fetch(tid + j * kCopyThreads);
+  const uint32_t tiles = ends[0];
+  if (tiles == kUnprepared) {
+    expand_block<kCopyThreads>(a, i, sm);
+  } else {
+    uint32_t q0 = 0;
+    for (uint32_t t = 0; t < tiles; t++) {
+      const uint32_t q1 = ends[1 + t];
+      if (t) __syncthreads();  // a tile reads the tiles before it
+      for (; q0 < q1; q0 += kCopyPer * kCopyThreads) {
+        if (q0) {
+#pragma unroll
+          for (uint32_t j = 0; j < kCopyPer; j++) r[j] = fetch(q0 + tid + j * kCopyThreads);
+        }
+        uint4 v[kCopyPer];
+#pragma unroll
+        for (uint32_t j = 0; j < kCopyPer; j++) v[j] = rec_load(r[j], q0 + tid + j * kCopyThreads < q1);
+#pragma unroll
+        for (uint32_t j = 0; j < kCopyPer; j++)
+          if (q0 + tid + j * kCopyThreads < q1) rec_store(r[j], v[j]);
+      }
+      q0 = q1;
+    }
+  }
+  if (a.trace && tid == 0) {
+    a.trace[8ull * i] = c0;
+    a.trace[8ull * i + 1] = (unsigned long long)wall_clock64();
+  }
+}
+
 // One of kMaxXcc times the wanted members: the workgroups on the XCD that the
 // first one to arrive runs on become the members, the others end.  Member 0
 // closes the door once every workgroup of the launch has arrived (or after
@@ -1905,7 +1971,7 @@ __device__ uint32_t chain_join(const ChainArgs& ch, uint32_t grid, uint32_t max_
   return rank;
 }
 
-// The levels [lv_lo, lv_hi), whose blocks k_prep recorded (at most
+// The levels [lv_lo, lv_hi), of levels that k_prep recorded (at most
 // kChainBlocks blocks and levels).  A step is one tile of every block of a
 // level (a tile reads the tiles before it); its records are dealt over the
 // members' threads.
@@ -1926,10 +1992,11 @@ __global__ __launch_bounds__(kChainThreads) __attribute__((amdgpu_waves_per_eu(2
   const uint32_t rank = sh_rank, members = sh_members;
   if (rank == kNoItem) return;
   const uint32_t p0 = a.lvl_dev[lv_lo], n_lv = lv_hi - lv_lo, n_blk = a.lvl_dev[lv_hi] - p0;
-  const uint4* recs = reinterpret_cast<const uint4*>(ch.recs);
+  const uint32_t slot0 = p0 - a.lvl_dev[ch.lv_base];
+  const uint4* recs = reinterpret_cast<const uint4*>(ch.recs) + (uint64_t)slot0 * ch.rec_cap;
   for (uint32_t l = tid; l <= n_lv; l += kChainThreads) s_lv[l] = a.lvl_dev[lv_lo + l] - p0;
   for (uint32_t j = tid; j < n_blk * kChainEnds; j += kChainThreads)
-    s_ends[j / kChainEnds][j % kChainEnds] = (uint16_t)ch.ends[j];
+    s_ends[j / kChainEnds][j % kChainEnds] = (uint16_t)ch.ends[(uint64_t)slot0 * kChainEnds + j];
   __syncthreads();
   // tile t of block b: its first record, and how many there are
   auto tile_of = [&](uint32_t b, uint32_t t, uint32_t& r0) -> uint32_t {
@@ -2555,11 +2622,37 @@ hipError_t launch_expand_level_dev(const DecodeArgs& a, uint32_t level, uint32_t
 // over later.
 constexpr uint32_t kChainGrid = 8 * 10;
 hipError_t launch_chain(const DecodeArgs& a, const ChainArgs& ch, uint32_t lv_lo, uint32_t lv_hi, uint32_t blocks,
-                        hipStream_t s) {
+                        uint32_t run, hipStream_t s) {
   if (blocks == 0 || lv_hi <= lv_lo) return hipSuccess;
-  if (blocks > kChainBlocks || lv_hi - lv_lo > kChainBlocks) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_prep, dim3(blocks), dim3(kPrepThreads), 0, s, a, ch, lv_lo, lv_hi);
-  hipLaunchKernelGGL(k_chain, dim3(kChainGrid), dim3(kChainThreads), 0, s, a, ch, lv_lo, lv_hi);
+  if (blocks > kChainBlocks || lv_hi - lv_lo > kChainBlocks || run >= kChainRuns) return hipErrorInvalidValue;
+  ChainArgs c = ch;
+  c.sync += (uint64_t)run * kChainSync;
+  hipLaunchKernelGGL(k_chain, dim3(kChainGrid), dim3(kChainThreads), 0, s, a, c, lv_lo, lv_hi);
+  return hipGetLastError();
+}
+
+// 512 threads a block while the blocks fit on the device two to a CU (then the
+// slowest block sets the time, and its walks are shared by more threads), else
+// 256, four to a CU.  A plan whose size is only known on the device gets both
+// launches, of which one ends at once: a 4 KB seek (240 blocks) records in 31 us
+// with 512 threads and 47 with 256, a range of 1,000 blocks (1,500 blocks) in 88
+// and 53.
+constexpr uint32_t kPrepWide = 512;
+hipError_t launch_prep(const DecodeArgs& a, const ChainArgs& ch, uint32_t lv_lo, uint32_t lv_hi, uint32_t blocks,
+                       bool exact, bool big_tiles, hipStream_t s) {
+  if (blocks == 0) return hipSuccess;
+  const bool wide = big_tiles || blocks <= kPrepWide, both = !exact && !wide;
+  if (wide || both)
+    hipLaunchKernelGGL(k_prep<512>, dim3(wide ? blocks : kPrepWide), dim3(512), 0, s, a, ch, lv_lo, lv_hi, 0u,
+                       wide ? blocks : kPrepWide);
+  if (!wide)
+    hipLaunchKernelGGL(k_prep<256>, dim3(blocks), dim3(256), 0, s, a, ch, lv_lo, lv_hi, both ? kPrepWide : 0u, blocks);
+  return hipGetLastError();
+}
+
+hipError_t launch_copy_level(const DecodeArgs& a, const ChainArgs& ch, uint32_t level, uint32_t blocks, hipStream_t s) {
+  if (blocks == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_copy_level, dim3(blocks), dim3(kCopyThreads), 0, s, a, ch, level);
   return hipGetLastError();
 }
 

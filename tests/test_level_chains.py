@@ -86,3 +86,49 @@ def test_chains_gpu(orc, case):
         bt.run((lo, hi), out)
         bt.check()
         assert out.cpu().numpy().tobytes() == b"".join(x[int(l):int(h)] for l, h in zip(lo, hi))
+
+
+# corpus, n, B, cap: groups of levels copied by a launch each; the last has
+# levels inside and outside the recorded groups
+GROUPS = [("text", 160_000, 200, 5), ("fastq", 1_500_000, 2000, 16), ("mixed", 4 << 20, 1000, 6)]
+
+
+def _capped(orc, case):
+    name, n, B, cap = case
+    x = gen.by_name(name, n, 43)
+    return x, orc.encode(x, block_size=B, interleave=16, min_match=16, hash_len=16, max_level=cap, flags=2)
+
+
+@pytest.mark.parametrize("case", GROUPS[:1], ids=lambda c: "%s-n%d-B%d-cap%d" % c)
+def test_recorded_groups_cpu_build(orc, case):
+    import simt_lib
+    x, a = _capped(orc, case)
+    arc = simt_lib.Archive(a)
+    assert arc.depth >= 3
+    assert arc.decode_all() == x
+    lo, hi = len(x) // 2 + 3, len(x) - 5
+    assert arc.seek(lo, hi) == x[lo:hi]
+    assert arc.seek_device(lo, hi) == x[lo:hi]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", GROUPS, ids=lambda c: "%s-n%d-B%d-cap%d" % c)
+def test_recorded_groups_gpu(orc, case):
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2606_24531_amd import Archive
+    x, a = _capped(orc, case)
+    for resident in (True, False):
+        arc = Archive(a, device="cuda:0", resident_plan=resident)
+        out = torch.zeros(len(x), dtype=torch.uint8, device="cuda:0")
+        arc.decode_all(out=out)
+        arc.check()
+        assert np.array_equal(out.cpu().numpy(), np.frombuffer(x, np.uint8))
+    arc = Archive(a, device="cuda:0")
+    lo, hi = gen.seek_requests(len(x), 5, 3, max_len=len(x))
+    for l, h in [(int(l), int(h)) for l, h in zip(lo, hi)] + [(0, len(x)), (len(x) - 1, len(x))]:
+        for plan in ("host", "device"):
+            got = arc.seek(l, h, plan=plan)
+            arc.check()
+            assert got.cpu().numpy().tobytes() == x[l:h], plan
