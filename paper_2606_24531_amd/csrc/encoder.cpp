@@ -30,13 +30,20 @@
 // only on the final levels of earlier epochs).
 #include <algorithm>
 #include <atomic>
+#include <condition_variable>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
+#include <memory>
+#include <mutex>
+#include <new>
 #include <string>
 #include <thread>
 #include <vector>
+
+#include <sys/mman.h>
 
 #include <hip/hip_runtime.h>
 
@@ -71,60 +78,183 @@ unsigned thread_count(uint32_t want) {
   return want ? want : hw;
 }
 
-template <class F>
-void parallel_for(uint64_t n, unsigned threads, F&& f) {
-  if (threads <= 1 || n < 2) {
-    for (uint64_t i = 0; i < n; i++) f(i);
-    return;
+// The call's threads, started once: an encode with a level cap runs one
+// parallel loop per epoch of 64 blocks.  run() deals the indexes below n over
+// the calling thread and the others and returns when all are done.
+class Pool {
+ public:
+  explicit Pool(unsigned threads) : threads_(threads ? threads : 1) {}
+  ~Pool() {
+    {
+      std::lock_guard<std::mutex> g(mu_);
+      stop_ = true;
+    }
+    wake_.notify_all();
+    for (auto& t : pool_) t.join();
   }
-  std::atomic<uint64_t> next{0};
-  std::vector<std::thread> pool;
-  for (unsigned t = 0; t < threads; t++)
-    pool.emplace_back([&] {
+  unsigned threads() const { return threads_; }
+  template <class F>
+  void run(uint64_t n, F&& f) {
+    if (threads_ <= 1 || n < 2) {
+      for (uint64_t i = 0; i < n; i++) f(i);
+      return;
+    }
+    std::atomic<uint64_t> next{0};
+    const std::function<void()> loop = [&] {
       for (uint64_t i; (i = next.fetch_add(1)) < n;) f(i);
-    });
-  for (auto& th : pool) th.join();
-}
+    };
+    {
+      std::lock_guard<std::mutex> g(mu_);
+      while (pool_.size() + 1 < threads_) pool_.emplace_back([this] { work(); });
+      job_ = &loop;
+      left_ = pool_.size();
+      round_++;
+    }
+    wake_.notify_all();
+    loop();
+    std::unique_lock<std::mutex> l(mu_);
+    idle_.wait(l, [&] { return left_ == 0; });
+    job_ = nullptr;
+  }
+
+ private:
+  void work() {
+    uint64_t seen = 0;
+    for (;;) {
+      const std::function<void()>* job;
+      {
+        std::unique_lock<std::mutex> l(mu_);
+        wake_.wait(l, [&] { return stop_ || (job_ && round_ != seen); });
+        if (stop_) return;
+        seen = round_;
+        job = job_;
+      }
+      (*job)();
+      std::lock_guard<std::mutex> g(mu_);
+      if (--left_ == 0) idle_.notify_all();
+    }
+  }
+  const unsigned threads_;
+  std::vector<std::thread> pool_;
+  std::mutex mu_;
+  std::condition_variable wake_, idle_;
+  const std::function<void()>* job_ = nullptr;
+  size_t left_ = 0;
+  uint64_t round_ = 0;
+  bool stop_ = false;
+};
 
 // ---------------------------------------------------------------------------
 // hash chains
 // ---------------------------------------------------------------------------
-struct Chains {
-  std::vector<uint32_t> prev;  // UINT32_MAX = none (positions < 2^32)
+// An uninitialised array in huge pages where the system grants them: the
+// threads that first touch a fresh array of 4 KiB pages spend longer in page
+// faults than on what they do with it.
+template <typename T>
+struct BigArray {
+  T* p = nullptr;
+  BigArray() = default;
+  explicit BigArray(uint64_t n) {
+    constexpr uint64_t kHuge = 2ull << 20;
+    const uint64_t bytes = rup(std::max<uint64_t>(1, n) * sizeof(T), bytes_step(n));
+    p = static_cast<T*>(aligned_alloc(bytes_step(n), bytes));
+    if (!p) throw std::bad_alloc();
+    if (bytes >= kHuge) (void)madvise(p, bytes, MADV_HUGEPAGE);
+  }
+  ~BigArray() { free(p); }
+  BigArray(const BigArray&) = delete;
+  BigArray& operator=(BigArray&& o) noexcept {
+    std::swap(p, o.p);
+    return *this;
+  }
+  T& operator[](uint64_t i) const { return p[i]; }
+
+ private:
+  static uint64_t bytes_step(uint64_t n) { return n * sizeof(T) >= (2ull << 20) ? 2ull << 20 : 64; }
 };
 
-void build_chains(const uint8_t* x, uint64_t n, uint32_t k, unsigned threads, Chains& C) {
+struct Chains {
+  BigArray<uint32_t> prev;  // UINT32_MAX = none (positions < 2^32); hashed positions only
+};
+
+// Positions are sorted by bucket range (in slices, each range's positions in
+// order), then every range is linked by itself with its part of the bucket
+// heads, which fits a core's cache: two passes over the positions where each
+// thread passing over all of them to pick its own took as many passes as
+// threads.  Up to kSegment positions at a time, so that the sorted ones take
+// 2 GiB at most.  8 MiB on 16 threads: 41 ms of page faults in small pages;
+// with huge ones the whole encode takes 25 ms, 78 before.
+void build_chains(const uint8_t* x, uint64_t n, uint32_t k, Pool& pool, Chains& C) {
+  constexpr uint64_t kSegment = 1ull << 28;
+  // with fewer threads, a pass each costs less than the sort (8 MiB encoded by
+  // one thread: 0.53 s against 0.87)
+  constexpr unsigned kSortThreads = 4;
   const uint32_t hb = hash_bits(n);
-  C.prev.assign(n, UINT32_MAX);
   if (n < k) return;
   const uint64_t npos = n - k + 1;
-  // bucket of every hashed position, in parallel over slices (rolling hash)
-  std::vector<uint32_t> bk(npos);
+  C.prev = BigArray<uint32_t>(npos);
+  const uint32_t shift = hb > 15 ? std::max(15u, hb - 8) : hb;  // buckets per range; at most 256 ranges
+  const uint32_t n_range = 1u << (hb - shift);
   uint32_t pk1 = 1;  // P^(k-1)
   for (uint32_t i = 0; i + 1 < k; i++) pk1 *= 0x01000193u;
-  const uint64_t slice = 1 << 20;
-  parallel_for((npos + slice - 1) / slice, threads, [&](uint64_t s) {
-    uint64_t q0 = s * slice, q1 = std::min(npos, q0 + slice);
+  // f(q, bucket) for the positions [q0, q1), by a rolling hash
+  auto buckets = [&](uint64_t q0, uint64_t q1, auto&& f) {
     uint32_t h = 0;
     for (uint32_t i = 0; i < k; i++) h = h * 0x01000193u + x[q0 + i];
     for (uint64_t q = q0; q < q1; q++) {
-      bk[q] = (uint32_t)(h * 0x9E3779B1u) >> (32 - hb);
+      f(q, (uint32_t)(h * 0x9E3779B1u) >> (32 - hb));
       if (q + k < n) h = (h - x[q] * pk1) * 0x01000193u + x[q + k];
     }
-  });
-  // link: each thread owns a range of buckets and scans every position
-  const unsigned T = std::max(1u, std::min(threads, 64u));
-  const uint64_t nbk = 1ull << hb;
-  parallel_for(T, T, [&](uint64_t t) {
-    const uint32_t lo = (uint32_t)(nbk * t / T), hi = (uint32_t)(nbk * (t + 1) / T);
-    std::vector<uint32_t> head(hi - lo, UINT32_MAX);
-    for (uint64_t q = 0; q < npos; q++) {
-      const uint32_t b = bk[q];
-      if (b < lo || b >= hi) continue;
-      C.prev[q] = head[b - lo];
-      head[b - lo] = (uint32_t)q;
+  };
+  BigArray<uint32_t> head(1ull << hb);
+  if (pool.threads() < kSortThreads) {  // each thread links a part of the buckets, over all positions
+    const uint64_t T = pool.threads(), nbk = 1ull << hb;
+    pool.run(T, [&](uint64_t t) {
+      const uint32_t lo = (uint32_t)(nbk * t / T), hi = (uint32_t)(nbk * (t + 1) / T);
+      std::fill(head.p + lo, head.p + hi, UINT32_MAX);
+      buckets(0, npos, [&](uint64_t q, uint32_t b) {
+        if (b < lo || b >= hi) return;
+        C.prev[q] = head[b];
+        head[b] = (uint32_t)q;
+      });
+    });
+    return;
+  }
+  BigArray<uint64_t> rec(std::min(npos, kSegment));
+  for (uint64_t s0 = 0; s0 < npos; s0 += kSegment) {
+    const uint64_t len = std::min(kSegment, npos - s0);
+    const uint64_t n_slice = std::max<uint64_t>(1, std::min<uint64_t>(4 * pool.threads(), len >> 16));
+    auto cut = [&](uint64_t s) { return s0 + len * s / n_slice; };
+    std::vector<std::vector<uint64_t>> at(n_slice);  // per slice and range: count, then place
+    pool.run(n_slice, [&](uint64_t s) {
+      std::vector<uint64_t> c(n_range, 0);
+      buckets(cut(s), cut(s + 1), [&](uint64_t, uint32_t b) { c[b >> shift]++; });
+      at[s].swap(c);
+    });
+    std::vector<uint64_t> start(n_range + 1, 0);
+    uint64_t pos = 0;
+    for (uint32_t r = 0; r < n_range; r++) {
+      start[r] = pos;
+      for (uint64_t s = 0; s < n_slice; s++) {
+        const uint64_t c = at[s][r];
+        at[s][r] = pos;
+        pos += c;
+      }
     }
-  });
+    start[n_range] = pos;
+    pool.run(n_slice, [&](uint64_t s) {
+      std::vector<uint64_t>& a = at[s];
+      buckets(cut(s), cut(s + 1), [&](uint64_t q, uint32_t b) { rec[a[b >> shift]++] = q << 32 | b; });
+    });
+    pool.run(n_range, [&](uint64_t r) {
+      if (s0 == 0) std::fill(head.p + (r << shift), head.p + ((r + 1) << shift), UINT32_MAX);
+      for (uint64_t i = start[r]; i < start[r + 1]; i++) {
+        const uint32_t q = (uint32_t)(rec[i] >> 32), b = (uint32_t)rec[i];
+        C.prev[q] = head[b];
+        head[b] = q;
+      }
+    });
+  }
 }
 
 inline uint32_t common_prefix(const uint8_t* a, const uint8_t* b, uint32_t lim) {
@@ -317,7 +447,7 @@ uint32_t offset_width(uint64_t n, uint32_t flags) {
 // The rANS step of every stream on the current device (the streams built,
 // each holding its raw symbols): one wavefront per stream, the same bytes
 // as code_stream.  Streams the device codes take mode 1 and the coded bytes.
-int device_entropy(std::vector<EncStream>& st, uint32_t W, uint32_t policy) {
+int device_entropy(std::vector<EncStream>& st, uint32_t W, uint32_t policy, Pool& pool) {
   const size_t ns = st.size();
   if (ns == 0) return ACE_OK;
   std::vector<uint64_t> sym_off(ns), out_off(ns), scr_off(ns);
@@ -329,50 +459,42 @@ int device_entropy(std::vector<EncStream>& st, uint32_t W, uint32_t policy) {
     out_off[i] = o;
     scr_off[i] = w;
     a += st[i].n_sym;
-    o += rup(544 + 4ull * W + 2ull * st[i].n_sym, 16);
+    // a stream that may stay raw is written only where it is smaller
+    o += rup(policy == 1 ? 544 + 4ull * W + 2ull * st[i].n_sym : st[i].n_sym, 16);
     w += st[i].n_sym;
   }
-  std::vector<uint8_t> sym(a ? a : 1);
-  for (size_t i = 0; i < ns; i++)
-    if (st[i].n_sym) memcpy(sym.data() + sym_off[i], st[i].data.data(), st[i].n_sym);
-  uint8_t *d_sym = nullptr, *d_out = nullptr;
-  uint64_t *d_soff = nullptr, *d_ooff = nullptr, *d_woff = nullptr;
-  uint32_t *d_n = nullptr, *d_len = nullptr;
-  uint16_t* d_scr = nullptr;
-  auto release = [&]() {
-    for (void* q : {(void*)d_sym, (void*)d_out, (void*)d_soff, (void*)d_ooff, (void*)d_woff, (void*)d_n,
-                    (void*)d_len, (void*)d_scr})
-      if (q) (void)hipFree(q);
-  };
+  std::unique_ptr<uint8_t[]> sym(new uint8_t[a ? a : 1]);
+  pool.run(ns, [&](uint64_t i) {
+    if (st[i].n_sym) memcpy(sym.get() + sym_off[i], st[i].data.data(), st[i].n_sym);
+  });
+  // one allocation: symbols, output, words, then the streams' tables
+  const uint64_t at_out = rup(a + 1, 256), at_scr = at_out + rup(o + 16, 256), at_tab = at_scr + rup(2 * w + 2, 256);
+  uint8_t* d = nullptr;
   auto hip = [&](hipError_t r, const char* what) {
     if (r == hipSuccess) return ACE_OK;
-    release();
+    if (d) (void)hipFree(d);
     return efail(ACE_E_HIP, "device entropy coding: %s: %s", what, hipGetErrorString(r));
   };
   int rc;
-  if ((rc = hip(hipMalloc((void**)&d_sym, sym.size()), "allocate symbols")) ||
-      (rc = hip(hipMalloc((void**)&d_out, o ? o : 16), "allocate output")) ||
-      (rc = hip(hipMalloc((void**)&d_scr, 2 * (w ? w : 1)), "allocate scratch")) ||
-      (rc = hip(hipMalloc((void**)&d_soff, 8 * ns), "allocate offsets")) ||
-      (rc = hip(hipMalloc((void**)&d_ooff, 8 * ns), "allocate offsets")) ||
-      (rc = hip(hipMalloc((void**)&d_woff, 8 * ns), "allocate offsets")) ||
-      (rc = hip(hipMalloc((void**)&d_n, 4 * ns), "allocate counts")) ||
-      (rc = hip(hipMalloc((void**)&d_len, 4 * ns), "allocate lengths")))
-    return rc;
-  if ((rc = hip(hipMemcpy(d_sym, sym.data(), sym.size(), hipMemcpyHostToDevice), "copy symbols")) ||
-      (rc = hip(hipMemcpy(d_soff, sym_off.data(), 8 * ns, hipMemcpyHostToDevice), "copy offsets")) ||
-      (rc = hip(hipMemcpy(d_ooff, out_off.data(), 8 * ns, hipMemcpyHostToDevice), "copy offsets")) ||
-      (rc = hip(hipMemcpy(d_woff, scr_off.data(), 8 * ns, hipMemcpyHostToDevice), "copy offsets")) ||
-      (rc = hip(hipMemcpy(d_n, nsym.data(), 4 * ns, hipMemcpyHostToDevice), "copy counts")))
+  if ((rc = hip(hipMalloc((void**)&d, at_tab + 32 * ns), "allocate buffers"))) return rc;
+  std::unique_ptr<uint8_t[]> tab(new uint8_t[28 * ns]);
+  memcpy(tab.get(), sym_off.data(), 8 * ns);
+  memcpy(tab.get() + 8 * ns, out_off.data(), 8 * ns);
+  memcpy(tab.get() + 16 * ns, scr_off.data(), 8 * ns);
+  memcpy(tab.get() + 24 * ns, nsym.data(), 4 * ns);
+  uint8_t* d_tab = d + at_tab;
+  uint32_t* d_len = reinterpret_cast<uint32_t*>(d_tab + 28 * ns);
+  if ((rc = hip(hipMemcpy(d, sym.get(), a, hipMemcpyHostToDevice), "copy symbols")) ||
+      (rc = hip(hipMemcpy(d_tab, tab.get(), 28 * ns, hipMemcpyHostToDevice), "copy tables")))
     return rc;
   ace::EncArgs e{};
-  e.sym = d_sym;
-  e.sym_off = d_soff;
-  e.n = d_n;
-  e.out = d_out;
-  e.out_off = d_ooff;
-  e.scratch = d_scr;
-  e.scr_off = d_woff;
+  e.sym = d;
+  e.sym_off = reinterpret_cast<const uint64_t*>(d_tab);
+  e.n = reinterpret_cast<const uint32_t*>(d_tab + 24 * ns);
+  e.out = d + at_out;
+  e.out_off = reinterpret_cast<const uint64_t*>(d_tab + 8 * ns);
+  e.scratch = reinterpret_cast<uint16_t*>(d + at_scr);
+  e.scr_off = reinterpret_cast<const uint64_t*>(d_tab + 16 * ns);
   e.out_len = d_len;
   e.W = W;
   e.policy = policy;
@@ -380,16 +502,16 @@ int device_entropy(std::vector<EncStream>& st, uint32_t W, uint32_t policy) {
   if ((rc = hip(ace::launch_rans_encode(e, nullptr), "launch")) || (rc = hip(hipDeviceSynchronize(), "run")))
     return rc;
   std::vector<uint32_t> len(ns);
-  std::vector<uint8_t> out(o ? o : 16);
+  std::unique_ptr<uint8_t[]> out(new uint8_t[o ? o : 16]);
   if ((rc = hip(hipMemcpy(len.data(), d_len, 4 * ns, hipMemcpyDeviceToHost), "copy lengths")) ||
-      (rc = hip(hipMemcpy(out.data(), d_out, out.size(), hipMemcpyDeviceToHost), "copy output")))
+      (rc = hip(hipMemcpy(out.get(), d + at_out, o ? o : 16, hipMemcpyDeviceToHost), "copy output")))
     return rc;
-  release();
-  for (size_t i = 0; i < ns; i++) {
-    if (!len[i]) continue;  // stays raw
+  (void)hipFree(d);
+  pool.run(ns, [&](uint64_t i) {
+    if (!len[i]) return;  // stays raw
     st[i].mode = 1;
-    st[i].data.assign(out.data() + out_off[i], out.data() + out_off[i] + len[i]);
-  }
+    st[i].data.assign(out.get() + out_off[i], out.get() + out_off[i] + len[i]);
+  });
   return ACE_OK;
 }
 
@@ -447,7 +569,7 @@ extern "C" int ace_encode_archive(const uint8_t* x, uint64_t n, const ace_encode
   int rc = check(n, p);
   if (rc) return rc;
   if ((!x && n) || !out_len) return efail(ACE_E_ARG, "null argument");
-  const unsigned T = thread_count(p->n_threads);
+  Pool pool(thread_count(p->n_threads));
   const uint64_t B = p->block_size, nb = n ? (n + B - 1) / B : 0;
   const uint32_t W = p->interleave, policy = p->flags & 3, ow = offset_width(n, p->flags);
   Chains C;
@@ -461,7 +583,22 @@ extern "C" int ace_encode_archive(const uint8_t* x, uint64_t n, const ace_encode
       fprintf(stderr, "[aceseek encode] parsed %llu of %llu blocks\n", (unsigned long long)done_blocks,
               (unsigned long long)nb), fflush(stderr);
   };
-  build_chains(x, n, p->hash_len, T, C);
+  // the checksum runs beside the rest (one multiply chain over the input)
+  uint64_t sum = 0xcbf29ce484222325ull;
+  auto checksum = [&] {
+    uint64_t h = sum;
+    for (uint64_t i = 0; i < n; i++) h = (h ^ x[i]) * 0x100000001b3ull;
+    sum = h;
+  };
+  struct Joined {
+    std::thread t;
+    ~Joined() {
+      if (t.joinable()) t.join();
+    }
+  } summing;
+  const bool beside = pool.threads() > 1 && n >= (1u << 16);
+  if (beside) summing.t = std::thread(checksum);
+  build_chains(x, n, p->hash_len, pool, C);
   if (progress) fprintf(stderr, "[aceseek encode] hash chains built (%llu bytes)\n", (unsigned long long)n), fflush(stderr);
   std::vector<std::vector<Seq>> seqs(nb);
   std::vector<uint32_t> level(nb, 0);
@@ -481,7 +618,7 @@ extern "C" int ace_encode_archive(const uint8_t* x, uint64_t n, const ace_encode
         deep.erase(std::remove_if(deep.begin(), deep.end(), [&](uint32_t b) { return level[b] < lam; }),
                    deep.end());
       }
-      parallel_for(e1 - e0, T, [&](uint64_t i) {
+      pool.run(e1 - e0, [&](uint64_t i) {
         parse_block(pc, e0 + i, true, seqs[e0 + i]);
         report(++parsed);
       });
@@ -494,7 +631,7 @@ extern "C" int ace_encode_archive(const uint8_t* x, uint64_t n, const ace_encode
       }
     }
   } else {
-    parallel_for(nb, T, [&](uint64_t b) {
+    pool.run(nb, [&](uint64_t b) {
       parse_block(pc, b, false, seqs[b]);
       report(++parsed);
     });
@@ -505,11 +642,11 @@ extern "C" int ace_encode_archive(const uint8_t* x, uint64_t n, const ace_encode
       level[b] = lv;
     }
   }
-  std::vector<uint32_t>().swap(C.prev);
+  C.prev = BigArray<uint32_t>();
   // streams, in parallel over blocks
   std::vector<EncStream> st(3 * nb);
   const bool device = (p->flags & ACE_ENC_DEVICE_ENTROPY) != 0;
-  parallel_for(nb, T, [&](uint64_t b) {
+  pool.run(nb, [&](uint64_t b) {
     const std::vector<Seq>& sq = seqs[b];
     std::vector<uint8_t> lit, lens(4 * sq.size()), offs(ow * sq.size());
     uint64_t pos = b * B;
@@ -532,7 +669,7 @@ extern "C" int ace_encode_archive(const uint8_t* x, uint64_t n, const ace_encode
     code_stream(lens.data(), (uint32_t)lens.size(), W, policy, st[3 * b + 1]);
     code_stream(offs.data(), (uint32_t)offs.size(), W, policy, st[3 * b + 2]);
   });
-  if (device && (rc = device_entropy(st, W, policy))) return rc;
+  if (device && (rc = device_entropy(st, W, policy, pool))) return rc;
   // layout
   uint64_t n_deps = 0, depth = 0;
   for (uint64_t b = 0; b < nb; b++) {
@@ -565,9 +702,9 @@ extern "C" int ace_encode_archive(const uint8_t* x, uint64_t n, const ace_encode
   put32(dst + 36, (uint32_t)n_deps);
   put64(dst + 40, 64);
   put64(dst + 48, pay_at);
-  uint64_t h = 0xcbf29ce484222325ull;
-  for (uint64_t i = 0; i < n; i++) h = (h ^ x[i]) * 0x100000001b3ull;
-  put64(dst + 56, h);
+  if (beside) summing.t.join();
+  else checksum();
+  put64(dst + 56, sum);
   uint64_t di = 0;
   for (uint64_t b = 0; b < nb; b++) {
     uint8_t* e = dst + 64 + 32 * b;
@@ -580,7 +717,7 @@ extern "C" int ace_encode_archive(const uint8_t* x, uint64_t n, const ace_encode
     for (uint32_t d : deps[b]) put32(dst + deps_at + 4 * (di++), d);
     (void)plen_end;
   }
-  parallel_for(nb, T, [&](uint64_t b) {
+  pool.run(nb, [&](uint64_t b) {
     uint8_t* pl = dst + pay[b];
     uint64_t off = 48;
     for (int t = 0; t < 3; t++) {
