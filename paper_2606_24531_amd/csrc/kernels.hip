@@ -2009,6 +2009,8 @@ __global__ __launch_bounds__(kChainThreads) __attribute__((amdgpu_waves_per_eu(2
     uint32_t l, t, n, tiles;  // level, tile; records of the step; tiles of the level's blocks, at most
   };
   auto open_step = [&](uint32_t l, uint32_t t) {
+    // levels that a seek's plan does not reach are passed over (no hand-over)
+    while (l < n_lv && s_lv[l + 1] == s_lv[l]) l++;
     Step s{l, t, 0, 1};
     if (l >= n_lv) return s;
     for (uint32_t b = s_lv[l]; b < s_lv[l + 1]; b++) {
