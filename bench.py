@@ -540,7 +540,10 @@ def finish(args, result, x, x_dev, a, arc, tuning, enc, d):
             ax = cached_archive(args, x, B, cap, enc)
             enc_s = time.time() - t0
             arcx = Archive(ax, device=dev)
-            e = decode_entry(arcx, ax, x_dev, tuning, steps, 1, key)
+            # the headline's launch shape was tuned on its own levels; without a
+            # level cap the library's own choice per level applies
+            shape = tuning if cap else dict(mode=1)
+            e = decode_entry(arcx, ax, x_dev, shape, steps, 1, key)
             algx = len(ax) + len(x) + e["ext"]
             extras[key] = {
                 "workload": "%s %d MiB, %d KiB blocks, %d-way rANS, %s" % (
