@@ -30,6 +30,19 @@ namespace {
 #ifndef ACE_OPAQUE
 #define ACE_OPAQUE(x) __asm__ volatile("" : "+v"(x))
 #endif
+// Waits until every store that this wavefront has issued is in its XCD's L2: a
+// store counts in vmcnt until the L2 has acknowledged it.  Neither a barrier
+// nor a fence of workgroup scope does that (they order memory between the
+// wavefronts of one CU, whose accesses pass the same vector cache in turn), so
+// a workgroup that tells another one of its stores calls this in every
+// wavefront, before the barrier that precedes the telling.
+__device__ __forceinline__ void wait_stores() {
+#ifdef __AMDGCN__
+  __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#else
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");  // a build for the host
+#endif
+}
 template <typename T>
 __device__ __forceinline__ ACE_GLOBAL T* gp(T* p) {
   return (ACE_GLOBAL T*)p;
@@ -2074,9 +2087,12 @@ __global__ __launch_bounds__(kChainThreads) __attribute__((amdgpu_waves_per_eu(2
           lds_barrier();
         }
       }
-      // hand over: every wave's stores have reached the XCD's L2 before its
-      // member is counted; the members' next loads miss the vector caches
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+      // hand over: every wave's stores are in the XCD's L2 before its member
+      // is counted (the counter may lie in another L2 channel than the bytes,
+      // so the order of issue says nothing; a decode of 192 levels takes 705 us
+      // with the wait, 677 without); the members' next loads miss the vector
+      // caches
+      wait_stores();
       __syncthreads();
       done += members;
       if (sn.l < n_lv) {
