@@ -2157,10 +2157,11 @@ __global__ __launch_bounds__(kChainThreads) __attribute__((amdgpu_waves_per_eu(2
 // block of the level is claimed, i.e. held by a running workgroup: the launch
 // needs no co-residency, and drains when it shares the device.
 //
-// Visibility across workgroups: every wave of a workgroup issues an
-// agent-scope release fence (its stores complete, this XCD's L2 written
-// back) before the barrier that precedes the workgroup's finished-count add;
-// the copies are raised by atomic max after that add.  A waiting workgroup
+// Visibility across workgroups: every wave of a workgroup waits until its
+// stores are in its XCD's L2 (wait_stores) before the barrier that precedes
+// the workgroup's count on that XCD; the last workgroup to leave the XCD writes
+// its L2 back (an agent-scope release) before it adds to the level's finished
+// count, and the copies are raised by atomic max after that add.  A waiting workgroup
 // polls with agent-scope atomic loads; a workgroup that claims a block of the
 // next level issues an agent-scope acquire fence in every wave before it
 // reads lower levels' bytes.
@@ -2236,14 +2237,14 @@ __global__ __launch_bounds__(kPersistThreads) __attribute__((amdgpu_waves_per_eu
         item = sh_item[par];
       }
       if (mine) {
-        // this workgroup's stores have reached its XCD's L2.  Leaving, it
+        // every wave's stores are in the XCD's L2.  Leaving, the workgroup
         // adds its blocks to the XCD's running count; the workgroup that
         // leaves the XCD with none expanding writes that L2 back once (an
         // agent-scope release, covering every block counted so far) and
         // raises the XCD's written-back count to the running count, adding
         // what it raised to the level's finished count.  A level is
         // complete once every XCD holding its bytes has written them back.
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        wait_stores();
         __syncthreads();
         if (tid < kPersistReplicas) {  // wave 0: lane r raises copy r
           uint32_t add = 0, prev = 0;

@@ -14,7 +14,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SRC = os.path.join(ROOT, "paper_2606_24531_amd", "csrc", "kernels.hip")
 
 # kernel, the returning atomic adds that publish a workgroup's stores
-CASES = [("k_chain", r"(global|flat)_atomic_add v")]
+CASES = [("k_chain", r"(global|flat)_atomic_add v"), ("k_persist", r"(global|flat)_atomic_add_x2 v")]
 
 
 @pytest.fixture(scope="module")
