@@ -35,6 +35,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <exception>
 #include <functional>
 #include <memory>
 #include <mutex>
@@ -80,7 +81,9 @@ unsigned thread_count(uint32_t want) {
 
 // The call's threads, started once: an encode with a level cap runs one
 // parallel loop per epoch of 64 blocks.  run() deals the indexes below n over
-// the calling thread and the others and returns when all are done.
+// the calling thread and the others (as many as could be started) and returns
+// when all are done; the first exception of a body ends the loop, and is thrown
+// again once no thread is in it.
 class Pool {
  public:
   explicit Pool(unsigned threads) : threads_(threads ? threads : 1) {}
@@ -100,21 +103,34 @@ class Pool {
       return;
     }
     std::atomic<uint64_t> next{0};
+    std::atomic<bool> failed{false};
+    std::exception_ptr error;  // written by the first body that throws
     const std::function<void()> loop = [&] {
-      for (uint64_t i; (i = next.fetch_add(1)) < n;) f(i);
+      try {
+        for (uint64_t i; (i = next.fetch_add(1)) < n;) f(i);
+      } catch (...) {
+        next = n;
+        if (!failed.exchange(true)) error = std::current_exception();
+      }
     };
     {
       std::lock_guard<std::mutex> g(mu_);
-      while (pool_.size() + 1 < threads_) pool_.emplace_back([this] { work(); });
+      try {
+        while (pool_.size() + 1 < threads_) pool_.emplace_back([this] { work(); });
+      } catch (...) {  // no memory or no thread left: those that run do the work
+      }
       job_ = &loop;
       left_ = pool_.size();
       round_++;
     }
     wake_.notify_all();
     loop();
-    std::unique_lock<std::mutex> l(mu_);
-    idle_.wait(l, [&] { return left_ == 0; });
-    job_ = nullptr;
+    {
+      std::unique_lock<std::mutex> l(mu_);
+      idle_.wait(l, [&] { return left_ == 0; });
+      job_ = nullptr;
+    }
+    if (error) std::rethrow_exception(error);
   }
 
  private:
