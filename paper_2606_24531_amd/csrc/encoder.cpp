@@ -485,14 +485,21 @@ int device_entropy(std::vector<EncStream>& st, uint32_t W, uint32_t policy, Pool
   });
   // one allocation: symbols, output, words, then the streams' tables
   const uint64_t at_out = rup(a + 1, 256), at_scr = at_out + rup(o + 16, 256), at_tab = at_scr + rup(2 * w + 2, 256);
-  uint8_t* d = nullptr;
   auto hip = [&](hipError_t r, const char* what) {
-    if (r == hipSuccess) return ACE_OK;
-    if (d) (void)hipFree(d);
-    return efail(ACE_E_HIP, "device entropy coding: %s: %s", what, hipGetErrorString(r));
+    return r == hipSuccess ? ACE_OK
+                           : efail(ACE_E_HIP, "device entropy coding: %s: %s", what, hipGetErrorString(r));
   };
   int rc;
-  if ((rc = hip(hipMalloc((void**)&d, at_tab + 32 * ns), "allocate buffers"))) return rc;
+  struct Free {
+    void operator()(uint8_t* q) const { (void)hipFree(q); }
+  };
+  std::unique_ptr<uint8_t, Free> buf;
+  {
+    void* q = nullptr;
+    if ((rc = hip(hipMalloc(&q, at_tab + 32 * ns), "allocate buffers"))) return rc;
+    buf.reset(static_cast<uint8_t*>(q));
+  }
+  uint8_t* d = buf.get();
   std::unique_ptr<uint8_t[]> tab(new uint8_t[28 * ns]);
   memcpy(tab.get(), sym_off.data(), 8 * ns);
   memcpy(tab.get() + 8 * ns, out_off.data(), 8 * ns);
@@ -522,7 +529,7 @@ int device_entropy(std::vector<EncStream>& st, uint32_t W, uint32_t policy, Pool
   if ((rc = hip(hipMemcpy(len.data(), d_len, 4 * ns, hipMemcpyDeviceToHost), "copy lengths")) ||
       (rc = hip(hipMemcpy(out.get(), d + at_out, o ? o : 16, hipMemcpyDeviceToHost), "copy output")))
     return rc;
-  (void)hipFree(d);
+  buf.reset();
   pool.run(ns, [&](uint64_t i) {
     if (!len[i]) return;  // stays raw
     st[i].mode = 1;
@@ -580,8 +587,8 @@ extern "C" int ace_encode_bound(uint64_t n, const ace_encode_params* p, uint64_t
   return ACE_OK;
 }
 
-extern "C" int ace_encode_archive(const uint8_t* x, uint64_t n, const ace_encode_params* p,
-                                  uint8_t* dst, uint64_t cap, uint64_t* out_len) {
+static int encode_archive(const uint8_t* x, uint64_t n, const ace_encode_params* p, uint8_t* dst, uint64_t cap,
+                          uint64_t* out_len) {
   int rc = check(n, p);
   if (rc) return rc;
   if ((!x && n) || !out_len) return efail(ACE_E_ARG, "null argument");
@@ -612,8 +619,12 @@ extern "C" int ace_encode_archive(const uint8_t* x, uint64_t n, const ace_encode
       if (t.joinable()) t.join();
     }
   } summing;
-  const bool beside = pool.threads() > 1 && n >= (1u << 16);
-  if (beside) summing.t = std::thread(checksum);
+  if (pool.threads() > 1 && n >= (1u << 16)) {
+    try {
+      summing.t = std::thread(checksum);
+    } catch (...) {  // no thread to be had: summed below
+    }
+  }
   build_chains(x, n, p->hash_len, pool, C);
   if (progress) fprintf(stderr, "[aceseek encode] hash chains built (%llu bytes)\n", (unsigned long long)n), fflush(stderr);
   std::vector<std::vector<Seq>> seqs(nb);
@@ -718,7 +729,7 @@ extern "C" int ace_encode_archive(const uint8_t* x, uint64_t n, const ace_encode
   put32(dst + 36, (uint32_t)n_deps);
   put64(dst + 40, 64);
   put64(dst + 48, pay_at);
-  if (beside) summing.t.join();
+  if (summing.t.joinable()) summing.t.join();
   else checksum();
   put64(dst + 56, sum);
   uint64_t di = 0;
@@ -754,4 +765,15 @@ extern "C" int ace_encode_archive(const uint8_t* x, uint64_t n, const ace_encode
     memset(pl + off, 0, next - (pay[b] + off));
   });
   return ACE_OK;
+}
+
+// No exception crosses the C boundary (the message is short: it allocates
+// nothing).
+extern "C" int ace_encode_archive(const uint8_t* x, uint64_t n, const ace_encode_params* p, uint8_t* dst,
+                                  uint64_t cap, uint64_t* out_len) {
+  try {
+    return encode_archive(x, n, p, dst, cap, out_len);
+  } catch (...) {
+    return efail(ACE_E_NOMEM, "out of memory");
+  }
 }
