@@ -75,7 +75,7 @@ struct ace_archive {
   // time, at most; the same for the whole archive, and for device-planned calls
   // (0: no group of the archive's levels is recorded)
   uint32_t rec_cap = 0, rec_blocks = 0, rec_all = 0, rec_dev = 0;
-  PlanEntry* all_plan_pinned = nullptr;
+  PlanEntry* all_plan_pinned = nullptr;  // all_plan, then all_levels
   const PlanEntry* d_plan = nullptr;  // the whole-archive plan resident on the device, if attached
   const uint32_t* d_order = nullptr;  // with it: all blocks by level, then the level boundaries
   const uint32_t* d_lstart = nullptr;
@@ -583,23 +583,24 @@ static int run_launches(const ace_archive* A, const PlanEntry* entries, uint64_t
                         const std::vector<uint32_t>& lstart, const CopyItem* items, uint64_t n_items,
                         const Layout& L, uint8_t* ws, uint64_t dst_base, const ace_tuning* t,
                         hipStream_t s, bool chain, bool loc_linear,
-                        const PlanEntry* resident, const uint8_t* arch);
+                        const PlanEntry* resident, const uint8_t* arch, const uint32_t* lv);
 
 // Runs a host-built plan (chain: runs of small levels may be chained, the
-// workspace holds L.total bytes); with phase timing on, also records the host time
-// spent planning (since the call's entry) and enqueueing.
+// workspace holds L.total bytes; lv: lstart's values in pinned memory that
+// outlives the call, if there is such a copy); with phase timing on, also
+// records the host time spent planning (since the call's entry) and enqueueing.
 static int run(const ace_archive* A, const PlanEntry* entries, uint64_t n_plan,
                const std::vector<uint32_t>& lstart, const CopyItem* items, uint64_t n_items,
                const Layout& L, uint8_t* ws, uint64_t dst_base, const ace_tuning* t,
-               hipStream_t s, bool chain, bool loc_linear = false,
-               const PlanEntry* resident = nullptr, const uint8_t* arch = nullptr) {
+               hipStream_t s, bool chain, bool loc_linear = false, const PlanEntry* resident = nullptr,
+               const uint8_t* arch = nullptr, const uint32_t* lv = nullptr) {
   if (!g_timer.on)
     return run_launches(A, entries, n_plan, lstart, items, n_items, L, ws, dst_base, t, s, chain,
-                        loc_linear, resident, arch);
+                        loc_linear, resident, arch, lv);
   const auto t_run = std::chrono::steady_clock::now();
   g_timer.us_plan = std::chrono::duration<double, std::micro>(t_run - g_timer.t_enter).count();
   const int rc = run_launches(A, entries, n_plan, lstart, items, n_items, L, ws, dst_base, t, s,
-                              chain, loc_linear, resident, arch);
+                              chain, loc_linear, resident, arch, lv);
   g_timer.us_enqueue = us_since(t_run);
   return rc;
 }
@@ -608,8 +609,9 @@ static int run_launches(const ace_archive* A, const PlanEntry* entries, uint64_t
                         const std::vector<uint32_t>& lstart, const CopyItem* items, uint64_t n_items,
                         const Layout& L, uint8_t* ws, uint64_t dst_base, const ace_tuning* t,
                         hipStream_t s, bool chain, bool loc_linear,
-                        const PlanEntry* resident, const uint8_t* arch) {
+                        const PlanEntry* resident, const uint8_t* arch, const uint32_t* lv) {
   if (!arch) arch = A->d_arch;  // an out-of-core seek passes its staged copy
+  if (!lv) lv = lstart.data();
   const uint32_t mode = t ? t->mode : 0;
   if (mode > 1 && mode != kModeOverlap && mode != kModePersistent) return fail(ACE_E_ARG, "unknown mode %u", mode);
   int rc = check_tuning(A, t);
@@ -678,7 +680,7 @@ static int run_launches(const ace_archive* A, const PlanEntry* entries, uint64_t
     if (mode == kModePersistent) {
       // the entropy launch, then one persistent launch for every level:
       // level boundaries uploaded, counters cleared by a fill kernel
-      HIP_TRY(hipMemcpyAsync(ws + L.lv, lstart.data(), 4ull * lstart.size(), hipMemcpyHostToDevice, s));
+      HIP_TRY(hipMemcpyAsync(ws + L.lv, lv, 4ull * lstart.size(), hipMemcpyHostToDevice, s));
       HIP_TRY(launch_fill_u32(a.lvl_done, 0u, persist_sync_words(a.n_lvl), s));
       HIP_TRY(entropy(0, (uint32_t)n_plan, s));
       if (timed) {
@@ -712,7 +714,7 @@ static int run_launches(const ace_archive* A, const PlanEntry* entries, uint64_t
         if (resident)
           a.lvl_dev = A->d_lstart;
         else
-          HIP_TRY(hipMemcpyAsync(ws + L.lv, lstart.data(), 4ull * lstart.size(), hipMemcpyHostToDevice, s));
+          HIP_TRY(hipMemcpyAsync(ws + L.lv, lv, 4ull * lstart.size(), hipMemcpyHostToDevice, s));
       }
       HIP_TRY(entropy(0, (uint32_t)n_plan, s));
       if (!recorded) {
@@ -778,21 +780,27 @@ extern "C" int ace_decode_all(const ace_archive* A, uint8_t* d_out, uint64_t out
                (uint64_t)(uintptr_t)d_out, t, static_cast<hipStream_t>(stream), true, true, A->d_plan);
   ace_archive* M = const_cast<ace_archive*>(A);
   const PlanEntry* entries = A->all_plan.data();
+  const uint32_t* lv = nullptr;
   {
     std::lock_guard<std::mutex> g(M->pin_mu);
     if (!M->all_plan_pinned) {
       void* p = nullptr;
-      if (hipHostMalloc(&p, sizeof(PlanEntry) * A->nb, hipHostMallocDefault) == hipSuccess) {
-        memcpy(p, A->all_plan.data(), sizeof(PlanEntry) * A->nb);
+      const size_t n_entry = sizeof(PlanEntry) * A->nb, n_lv = 4ull * A->all_levels.size();
+      if (hipHostMalloc(&p, n_entry + n_lv, hipHostMallocDefault) == hipSuccess) {
+        memcpy(p, A->all_plan.data(), n_entry);
+        memcpy(static_cast<uint8_t*>(p) + n_entry, A->all_levels.data(), n_lv);
         M->all_plan_pinned = static_cast<PlanEntry*>(p);
       } else {
         (void)hipGetLastError();
       }
     }
-    if (M->all_plan_pinned) entries = M->all_plan_pinned;
+    if (M->all_plan_pinned) {
+      entries = M->all_plan_pinned;
+      lv = reinterpret_cast<const uint32_t*>(entries + A->nb);
+    }
   }
   return run(A, entries, A->nb, A->all_levels, nullptr, 0, L, static_cast<uint8_t*>(d_ws),
-             (uint64_t)(uintptr_t)d_out, t, static_cast<hipStream_t>(stream), true, true);
+             (uint64_t)(uintptr_t)d_out, t, static_cast<hipStream_t>(stream), true, true, nullptr, nullptr, lv);
 }
 
 // The resident plan: the entries, then the blocks by level and the level

@@ -10,6 +10,7 @@
 #include <ucontext.h>
 
 #include <chrono>
+#include <map>
 #include <mutex>
 #include <thread>
 #include <vector>
@@ -348,7 +349,21 @@ hipError_t hipGetLastError() {
 hipError_t hipPeekAtLastError() { return simt::t_err; }
 const char* hipGetErrorString(hipError_t e) { return e == hipSuccess ? "no error" : "simulated error"; }
 
-hipError_t hipMemcpyAsync(void* dst, const void* src, size_t n, hipMemcpyKind, hipStream_t s) {
+// Allocations of the runtime; copies from the host on a stream whose source is
+// in none of them (such a copy is not asynchronous, and a captured one reads
+// memory that its caller may free).
+static std::mutex g_alloc_mu;
+static std::map<const char*, size_t> g_alloc;
+static std::atomic<uint64_t> g_pageable{0};
+extern "C" uint64_t simt_pageable_copies() { return g_pageable.exchange(0); }
+static bool allocated(const void* p, size_t n) {
+  std::lock_guard<std::mutex> g(g_alloc_mu);
+  auto it = g_alloc.upper_bound(static_cast<const char*>(p));
+  return it != g_alloc.begin() && (--it, static_cast<const char*>(p) + n <= it->first + it->second);
+}
+
+hipError_t hipMemcpyAsync(void* dst, const void* src, size_t n, hipMemcpyKind k, hipStream_t s) {
+  if (k == hipMemcpyHostToDevice && n && !allocated(src, n)) g_pageable++;
   if (s && s->capturing) {
     s->ops.push_back([dst, src, n]() { memcpy(dst, src, n); });
     return hipSuccess;
@@ -369,9 +384,16 @@ hipError_t hipMemsetAsync(void* dst, int v, size_t n, hipStream_t s) {
 }
 hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
   *p = malloc(n ? n : 1);
-  return *p ? hipSuccess : hipErrorUnknown;
+  if (!*p) return hipErrorUnknown;
+  std::lock_guard<std::mutex> g(g_alloc_mu);
+  g_alloc[static_cast<const char*>(*p)] = n;
+  return hipSuccess;
 }
 hipError_t hipHostFree(void* p) {
+  {
+    std::lock_guard<std::mutex> g(g_alloc_mu);
+    g_alloc.erase(static_cast<const char*>(p));
+  }
   free(p);
   return hipSuccess;
 }
