@@ -72,8 +72,8 @@ struct ace_archive {
   std::vector<uint32_t> all_levels;
   uint64_t all_seq = 0;
   // copy records: per block; the blocks of a host-planned call recorded at a
-  // time, at most; the same for the whole archive, and for device-planned calls
-  // (0: no group of the archive's levels is recorded)
+  // time, at most; the largest group of the whole archive's levels that is
+  // recorded, and the largest in device-planned calls (0: none is)
   uint32_t rec_cap = 0, rec_blocks = 0, rec_all = 0, rec_dev = 0;
   PlanEntry* all_plan_pinned = nullptr;  // all_plan, then all_levels
   const PlanEntry* d_plan = nullptr;  // the whole-archive plan resident on the device, if attached
@@ -289,6 +289,14 @@ static std::vector<LevelRun> level_runs(const std::vector<uint32_t>& lstart, uin
   return runs;
 }
 
+// The blocks of the largest recorded group: the record slots that the plan needs.
+static uint32_t record_slots(const std::vector<uint32_t>& lstart, uint32_t max_blocks, uint32_t B) {
+  uint32_t n = 0;
+  for (const LevelRun& r : level_runs(lstart, max_blocks, B))
+    if (r.op == LevelOp::record) n = std::max(n, lstart[r.hi] - lstart[r.lo]);
+  return n;
+}
+
 extern "C" int ace_archive_open(const uint8_t* h_arch, uint64_t len, const void* d_arch,
                                 ace_archive** out) {
   if (!h_arch || !out) return fail(ACE_E_ARG, "null argument");
@@ -321,11 +329,8 @@ extern "C" int ace_archive_open(const uint8_t* h_arch, uint64_t len, const void*
   A->rec_cap = A->B / 8 + 512;
   const uint64_t fit = A->depth >= kChainRun && A->rec_cap <= kMaxRecs ? kRecBytes / (16ull * A->rec_cap) : 0;
   A->rec_blocks = (uint32_t)std::min<uint64_t>(kRecBlocks, fit);
-  const uint32_t dev = (uint32_t)std::min<uint64_t>(kRecBlocksDev, fit);
-  for (const LevelRun& r : level_runs(A->all_levels, A->rec_blocks, A->B))
-    if (r.op == LevelOp::record) A->rec_all = std::min(A->rec_blocks, A->nb);
-  for (const LevelRun& r : level_runs(A->all_levels, dev, A->B))
-    if (r.op == LevelOp::record) A->rec_dev = std::min(dev, A->nb);
+  A->rec_all = record_slots(A->all_levels, A->rec_blocks, A->B);
+  A->rec_dev = record_slots(A->all_levels, (uint32_t)std::min<uint64_t>(kRecBlocksDev, fit), A->B);
   *out = A;
   return ACE_OK;
 }
@@ -512,10 +517,9 @@ hipError_t run_levels(const ace_archive* A, const DecodeArgs& a, const std::vect
 // Workspace of one host-planned decode.  lv: per dependency level of the
 // archive, the plan's level boundaries (depth + 1), then the persistent
 // kernel's finished counts (depth) and its finished-level copies.
-// Workspace of a plan of n_plan blocks (whole: all of the archive's, in its
-// own level sizes).
+// Workspace of a plan of n_plan blocks, with records of n_rec blocks.
 Layout layout(const ace_archive* A, uint64_t n_plan, uint64_t n_seq, uint64_t n_slots, uint64_t n_items,
-              bool whole = false) {
+              uint64_t n_rec) {
   Layout L;
   uint64_t o = kWsHeader;
   L.plan = o;  o = align_up(o + sizeof(PlanEntry) * n_plan, 256);
@@ -526,7 +530,7 @@ Layout layout(const ace_archive* A, uint64_t n_plan, uint64_t n_seq, uint64_t n_
   L.offs = o;  o = align_up(o + (uint64_t)A->ow * n_seq, 256);
   L.slots = o; o = align_up(o + (uint64_t)A->B * n_slots, 256);
   L.items = o; o = align_up(o + sizeof(CopyItem) * n_items, 256);
-  layout_records(A, whole ? A->rec_all : std::min<uint64_t>(A->rec_blocks, n_plan), L, o);
+  layout_records(A, n_rec, L, o);
   return L;
 }
 
@@ -585,7 +589,7 @@ static int run_launches(const ace_archive* A, const PlanEntry* entries, uint64_t
                         hipStream_t s, bool chain, bool loc_linear,
                         const PlanEntry* resident, const uint8_t* arch, const uint32_t* lv);
 
-// Runs a host-built plan (chain: runs of small levels may be chained, the
+// Runs a host-built plan (chain: groups of small levels may be recorded, the
 // workspace holds L.total bytes; lv: lstart's values in pinned memory that
 // outlives the call, if there is such a copy); with phase timing on, also
 // records the host time spent planning (since the call's entry) and enqueueing.
@@ -706,8 +710,7 @@ static int run_launches(const ace_archive* A, const PlanEntry* entries, uint64_t
       for (size_t l = split; l < nl; l++) HIP_TRY(expand(l));
     } else {
       std::vector<LevelRun> runs;
-      if (chain && waves == 0)
-        runs = level_runs(lstart, resident ? A->rec_all : (uint32_t)std::min<uint64_t>(A->rec_blocks, n_plan), A->B);
+      if (chain && waves == 0) runs = level_runs(lstart, A->rec_blocks, A->B);
       const bool recorded =
           std::any_of(runs.begin(), runs.end(), [](const LevelRun& r) { return r.op == LevelOp::record; });
       if (recorded) {  // the kernels read the level boundaries on the device
@@ -741,7 +744,7 @@ extern "C" int ace_workspace_bytes(const ace_archive* A, const ace_range* r, uin
                                    uint64_t* bytes) {
   if (!A || !bytes || (n && !r)) return fail(ACE_E_ARG, "null argument");
   if (n == 0) {
-    *bytes = layout(A, A->nb, A->all_seq, 0, 0, true).total;
+    *bytes = layout(A, A->nb, A->all_seq, 0, 0, A->rec_all).total;
     return ACE_OK;
   }
   std::vector<uint8_t> need(A->nb, 0);
@@ -758,11 +761,12 @@ extern "C" int ace_workspace_bytes(const ace_archive* A, const ace_range* r, uin
     items += (r[i].hi - r[i].lo + 65535) / 65536 + 2;
     any = true;
   }
-  std::vector<uint32_t> blocks;
+  std::vector<uint32_t> blocks, order, lstart;
   if (any) close_set(A, need, top, blocks);
+  level_order(A, blocks, order, lstart);
   uint64_t seq = 0;
   for (uint32_t b : blocks) seq += A->blk[b].n_seq;
-  *bytes = layout(A, blocks.size(), seq, blocks.size(), items).total;
+  *bytes = layout(A, blocks.size(), seq, blocks.size(), items, record_slots(lstart, A->rec_blocks, A->B)).total;
   return ACE_OK;
 }
 
@@ -772,7 +776,7 @@ extern "C" int ace_decode_all(const ace_archive* A, uint8_t* d_out, uint64_t out
   if (!A || (!d_out && A->n) || !d_ws) return fail(ACE_E_ARG, "null argument");
   if (int rc = need_resident(A)) return rc;
   if (out_cap < A->n) return fail(ACE_E_NOSPACE, "output needs %llu bytes", (unsigned long long)A->n);
-  Layout L = layout(A, A->nb, A->all_seq, 0, 0, true);
+  Layout L = layout(A, A->nb, A->all_seq, 0, 0, A->rec_all);
   if (ws_cap < L.total) return fail(ACE_E_NOSPACE, "workspace needs %llu bytes", (unsigned long long)L.total);
   if (A->nb == 0) return ACE_OK;
   if (A->d_plan)
@@ -885,7 +889,7 @@ static int seek_impl(const ace_archive* A, uint64_t lo, uint64_t hi, uint8_t* d_
     const uint64_t s0 = std::max(lo, bs), s1 = std::min(hi, be);
     items.push_back(CopyItem{s0, (uint64_t)(uintptr_t)d_out + (s0 - lo), (uint32_t)(s1 - s0), 0});
   }
-  Layout L = layout(A, order.size(), seq, n_slots, items.size());
+  Layout L = layout(A, order.size(), seq, n_slots, items.size(), record_slots(lstart, A->rec_blocks, A->B));
   // the allocation-free seek has a fixed scratch and may be captured: it keeps
   // to a launch per level, without copy records
   const uint64_t needs = allow_device ? L.total : L.base;
@@ -929,6 +933,13 @@ struct OocSeek {
   uint64_t gap = 0, stage = 0, total = 0;
 };
 
+// The workspace of a planned seek, with records of n_rec blocks.
+void ooc_place(const ace_archive* A, OocSeek& P, uint32_t n_rec) {
+  P.L = layout(A, P.order.size(), P.seq, P.n_slots, P.items.size(), n_rec);
+  P.stage = align_up(std::max(P.L.total, P.gap), 256);
+  P.total = P.stage + align_up(P.deps_bytes, 16) + P.pay_bytes + ACE_ARCH_PAD;
+}
+
 void ooc_plan(const ace_archive* A, uint64_t lo, uint64_t hi, uint8_t* d_out, OocSeek& P) {
   const uint32_t t0 = (uint32_t)(lo / A->B), t1 = (uint32_t)((hi - 1) / A->B);
   std::vector<uint32_t> blocks;
@@ -953,10 +964,8 @@ void ooc_plan(const ace_archive* A, uint64_t lo, uint64_t hi, uint8_t* d_out, Oo
     const uint64_t s0 = std::max(lo, bs), s1 = std::min(hi, be);
     P.items.push_back(CopyItem{s0, (uint64_t)(uintptr_t)d_out + (s0 - lo), (uint32_t)(s1 - s0), 0});
   }
-  P.L = layout(A, P.order.size(), P.seq, P.n_slots, P.items.size());
   P.gap = kHdr + (uint64_t)kBlk * A->nb;
-  P.stage = align_up(std::max(P.L.total, P.gap), 256);
-  P.total = P.stage + align_up(P.deps_bytes, 16) + P.pay_bytes + ACE_ARCH_PAD;
+  ooc_place(A, P, record_slots(P.lstart, A->rec_blocks, A->B));
 }
 }  // namespace
 
@@ -1101,7 +1110,7 @@ extern "C" int ace_seek_batch(const ace_archive* A, const ace_range* r, uint32_t
   level_order(A, blocks, order, lstart);
   uint64_t seq = 0;
   for (uint32_t b : order) seq += A->blk[b].n_seq;
-  Layout L = layout(A, order.size(), seq, order.size(), items.size());
+  Layout L = layout(A, order.size(), seq, order.size(), items.size(), record_slots(lstart, A->rec_blocks, A->B));
   if (ws_cap < L.total) return fail(ACE_E_NOSPACE, "workspace needs %llu bytes", (unsigned long long)L.total);
   uint8_t* ws = static_cast<uint8_t*>(d_ws);
   std::vector<PlanEntry> entries(order.size());
@@ -1320,7 +1329,7 @@ extern "C" int ace_workspace_bound(const ace_archive* A, uint32_t n_ranges, uint
   // ranges can need: a range of len bytes takes at most len / 64 KiB + 3
   // (the layout grows with each of these)
   const uint64_t items = total_bytes / 65536 + 3ull * n_ranges;
-  *bytes = layout(A, A->nb, A->all_seq, A->nb, items).total;
+  *bytes = layout(A, A->nb, A->all_seq, A->nb, items, std::min(A->rec_blocks, A->nb)).total;
   return ACE_OK;
 }
 
