@@ -98,7 +98,9 @@ typedef struct {
  *                   groups of levels of few blocks are turned into copy
  *                   records by one launch and then copied level by level,
  *                   long runs of small levels within one launch; the
- *                   workspace sizes below include the records); 2: one entropy launch,
+ *                   workspace sizes below include the records, and a seek
+ *                   whose workspace holds all but them does with a launch
+ *                   per level); 2: one entropy launch,
  *                   then one persistent launch that expands every level in
  *                   turn, synchronised by counters in the workspace (every
  *                   wait bounded by a count of idle polls: an expired wait

@@ -890,11 +890,10 @@ static int seek_impl(const ace_archive* A, uint64_t lo, uint64_t hi, uint8_t* d_
     items.push_back(CopyItem{s0, (uint64_t)(uintptr_t)d_out + (s0 - lo), (uint32_t)(s1 - s0), 0});
   }
   Layout L = layout(A, order.size(), seq, n_slots, items.size(), record_slots(lstart, A->rec_blocks, A->B));
-  // the allocation-free seek has a fixed scratch and may be captured: it keeps
-  // to a launch per level, without copy records
-  const uint64_t needs = allow_device ? L.total : L.base;
-  if (ws_need) *ws_need = needs;
-  if (ws_cap < needs) return fail(ACE_E_NOSPACE, "workspace needs %llu bytes", (unsigned long long)needs);
+  // a workspace without room for the records does with a launch per level; so
+  // does the allocation-free seek, which has a fixed scratch and may be captured
+  if (ws_need) *ws_need = L.base;
+  if (ws_cap < L.base) return fail(ACE_E_NOSPACE, "workspace needs %llu bytes", (unsigned long long)L.base);
   uint8_t* ws = static_cast<uint8_t*>(d_ws);
   uint64_t slot = 0;
   for (size_t i = 0; i < order.size(); i++) {
@@ -903,7 +902,7 @@ static int seek_impl(const ace_archive* A, uint64_t lo, uint64_t hi, uint8_t* d_
                                : (uint64_t)(uintptr_t)(ws + L.slots) + (slot++) * A->B;
   }
   return run(A, entries.data(), entries.size(), lstart, items.data(), items.size(), L, ws, 0, t,
-             static_cast<hipStream_t>(stream), allow_device);
+             static_cast<hipStream_t>(stream), allow_device && ws_cap >= L.total);
 }
 
 extern "C" int ace_seek(const ace_archive* A, uint64_t lo, uint64_t hi, uint8_t* d_out, void* d_ws,
@@ -999,6 +998,8 @@ extern "C" int ace_seek_ooc(const ace_archive* A, uint64_t lo, uint64_t hi, uint
   hipStream_t s = static_cast<hipStream_t>(stream);
   OocSeek P;
   ooc_plan(A, lo, hi, d_out, P);
+  const bool records = ws_cap >= P.total;
+  if (!records) ooc_place(A, P, 0);  // a launch per level, if the rest fits
   if (ws_cap < P.total) return fail(ACE_E_NOSPACE, "workspace needs %llu bytes", (unsigned long long)P.total);
   uint8_t* ws = static_cast<uint8_t*>(d_ws);
   uint64_t slot = 0;
@@ -1049,7 +1050,7 @@ extern "C" int ace_seek_ooc(const ace_archive* A, uint64_t lo, uint64_t hi, uint
   }
   if (staged > sent) HIP_TRY(hipMemcpyAsync(ws + P.stage + sent, h + sent, staged - sent, hipMemcpyHostToDevice, s));
   const int rc = run(A, P.entries.data(), P.entries.size(), P.lstart, P.items.data(), P.items.size(), P.L, ws, 0,
-                     t, s, true, false, nullptr, ws + P.stage - P.gap);
+                     t, s, records, false, nullptr, ws + P.stage - P.gap);
   if (rc) return rc;
   HIP_TRY(hipStreamSynchronize(s));
   return ACE_OK;
@@ -1111,7 +1112,7 @@ extern "C" int ace_seek_batch(const ace_archive* A, const ace_range* r, uint32_t
   uint64_t seq = 0;
   for (uint32_t b : order) seq += A->blk[b].n_seq;
   Layout L = layout(A, order.size(), seq, order.size(), items.size(), record_slots(lstart, A->rec_blocks, A->B));
-  if (ws_cap < L.total) return fail(ACE_E_NOSPACE, "workspace needs %llu bytes", (unsigned long long)L.total);
+  if (ws_cap < L.base) return fail(ACE_E_NOSPACE, "workspace needs %llu bytes", (unsigned long long)L.base);
   uint8_t* ws = static_cast<uint8_t*>(d_ws);
   std::vector<PlanEntry> entries(order.size());
   uint64_t sq = 0;
@@ -1120,7 +1121,7 @@ extern "C" int ace_seek_batch(const ace_archive* A, const ace_range* r, uint32_t
     sq += A->blk[order[i]].n_seq;
   }
   return run(A, entries.data(), entries.size(), lstart, items.data(), items.size(), L, ws, 0, t,
-             static_cast<hipStream_t>(stream), true);
+             static_cast<hipStream_t>(stream), ws_cap >= L.total);
 }
 
 extern "C" int ace_check(void* d_ws, void* stream) {
