@@ -116,7 +116,6 @@ struct BatchArgs {
   uint64_t n_total;
   const uint32_t* lstart;  // level boundaries in `all` (depth + 1, static)
   uint8_t* need;           // per block: needed by this batch
-  uint32_t* pre;           // per position in `all`: needed blocks before it
   const uint64_t* desc;
   PlanEntry* plan;
   uint32_t* n_plan_dev;

@@ -77,8 +77,7 @@ struct ace_archive {
   uint32_t rec_cap = 0, rec_blocks = 0, rec_all = 0, rec_dev = 0;
   PlanEntry* all_plan_pinned = nullptr;  // all_plan, then all_levels
   const PlanEntry* d_plan = nullptr;  // the whole-archive plan resident on the device, if attached
-  const uint32_t* d_order = nullptr;  // with it: all blocks by level, then the level boundaries
-  const uint32_t* d_lstart = nullptr;
+  const uint32_t* d_lstart = nullptr;  // its level boundaries
   std::mutex pin_mu;
   // out of core: the archive stays in host memory (h_arch, the caller's);
   // each seek stages what it needs through a pinned buffer
@@ -807,8 +806,9 @@ extern "C" int ace_decode_all(const ace_archive* A, uint8_t* d_out, uint64_t out
              (uint64_t)(uintptr_t)d_out, t, static_cast<hipStream_t>(stream), true, true, nullptr, nullptr, lv);
 }
 
-// The resident plan: the entries, then the blocks by level and the level
-// boundaries (the static data of device-side seek planning).
+// The resident plan: the entries, then the block ids in that order (part of
+// the buffer's stated layout; the kernels read them in the entries) and the
+// level boundaries (the static data of device-side seek planning).
 static uint64_t plan_bytes(const ace_archive* A) {
   return sizeof(PlanEntry) * (uint64_t)A->nb + 4ull * A->nb + 4ull * (A->depth + 1);
 }
@@ -835,7 +835,6 @@ extern "C" int ace_archive_attach_plan(ace_archive* A, void* d_plan, uint64_t by
   HIP_TRY(hipMemcpyAsync(d + o_lstart, A->all_levels.data(), 4ull * (A->depth + 1), hipMemcpyHostToDevice, s));
   HIP_TRY(hipStreamSynchronize(s));
   A->d_plan = reinterpret_cast<const PlanEntry*>(d);
-  A->d_order = reinterpret_cast<const uint32_t*>(d + o_order);
   A->d_lstart = reinterpret_cast<const uint32_t*>(d + o_lstart);
   return ACE_OK;
 }
@@ -861,7 +860,7 @@ static int seek_impl(const ace_archive* A, uint64_t lo, uint64_t hi, uint8_t* d_
                              (unsigned long long)A->n);
   if (lo == hi) return ACE_OK;
   if (!d_out || !d_ws) return fail(ACE_E_ARG, "null argument");
-  if (allow_device && A->d_order && ws_cap >= seek_device_bytes(A)) {
+  if (allow_device && A->d_plan && ws_cap >= seek_device_bytes(A)) {
     if (ws_need) *ws_need = seek_device_bytes(A);
     return seek_device(A, lo, hi, d_out, static_cast<uint8_t*>(d_ws), t, static_cast<hipStream_t>(stream));
   }
@@ -1173,7 +1172,7 @@ struct ace_batch {
 
 namespace {
 struct BatchLayout {
-  uint64_t lstart, need, pre, plan, nplan, lvl, loc, lit, lens, offs, slots, desc, pin, pinbase,
+  uint64_t lstart, need, plan, nplan, lvl, loc, lit, lens, offs, slots, desc, pin, pinbase,
       chunks, all, base, ends, sync, recs, total;
 };
 
@@ -1187,7 +1186,6 @@ BatchLayout batch_layout(const ace_archive* A, uint32_t cap) {
   };
   L.lstart = take(4ull * (A->depth + 1));
   L.need = take(align_up(A->nb, 4));
-  L.pre = take(4ull * A->nb);
   L.plan = take(sizeof(PlanEntry) * A->nb);
   L.nplan = take(4);
   L.lvl = take(4ull * (persist_row(A->depth + 1) + persist_sync_words(A->depth)));  // plan boundaries, then the persistent kernel's counters
@@ -1240,7 +1238,6 @@ static int seek_device(const ace_archive* A, uint64_t lo, uint64_t hi, uint8_t* 
   ba.n_total = A->n;
   ba.lstart = A->d_lstart;
   ba.need = ws + L.need;
-  ba.pre = reinterpret_cast<uint32_t*>(ws + L.pre);
   ba.desc = reinterpret_cast<const uint64_t*>(ws + L.desc);
   ba.plan = reinterpret_cast<PlanEntry*>(ws + L.plan);
   ba.n_plan_dev = reinterpret_cast<uint32_t*>(ws + L.nplan);
@@ -1397,7 +1394,6 @@ extern "C" int ace_batch_create(const ace_archive* A, uint32_t cap, void* d_ws, 
     ba.n_total = A->n;
     ba.lstart = reinterpret_cast<const uint32_t*>(b->ws + L.lstart);
     ba.need = b->ws + L.need;
-    ba.pre = reinterpret_cast<uint32_t*>(b->ws + L.pre);
     ba.desc = reinterpret_cast<const uint64_t*>(b->ws + L.desc);
     ba.plan = reinterpret_cast<PlanEntry*>(b->ws + L.plan);
     ba.n_plan_dev = reinterpret_cast<uint32_t*>(b->ws + L.nplan);

@@ -1817,7 +1817,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kThrea
 // levels 3.10 -> 0.69 ms, 1 MiB genome of 27 levels 0.51 -> 0.18 ms, 6 MiB
 // FASTQ 4.05 -> 0.85 ms, 6 MiB text in 64 KiB blocks 6.5 -> 0.82 ms.
 // ---------------------------------------------------------------------------
-constexpr uint32_t kChainThreads = 512, kChainPer = 1;
+constexpr uint32_t kChainThreads = 512;
 
 // Records of the blocks of levels [lv_lo, lv_hi) of the plan, one workgroup
 // each, in slots from 0 on; nothing unless they are more than n_lo and at most
@@ -2034,39 +2034,30 @@ __global__ __launch_bounds__(kChainThreads) __attribute__((amdgpu_waves_per_eu(2
     }
     return s;
   };
-  // records q0 + (j * members + rank) * kChainThreads + tid of the step,
-  // numbered through its blocks: the record, and a bit for whether there is one
-  uint4 cur[kChainPer], nxt[kChainPer];
-  const uint32_t lane0 = rank * kChainThreads + tid, stride = members * kChainThreads, batch = kChainPer * stride;
-  auto fetch = [&](const Step& s, uint32_t q0, uint4(&r)[kChainPer]) -> uint32_t {
-    uint32_t on = 0, rem = q0 + lane0, b = 0, hi = 0;
+  // record q0 + rank * kChainThreads + tid of the step, numbered through its
+  // blocks; false: there is none
+  uint4 cur, nxt;
+  const uint32_t lane0 = rank * kChainThreads + tid, batch = members * kChainThreads;
+  auto fetch = [&](const Step& s, uint32_t q0, uint4& r) -> bool {
+    uint32_t rem = q0 + lane0, b = 0, hi = 0, r0 = 0;
     if (s.l < n_lv) {
       b = s_lv[s.l];
       hi = s_lv[s.l + 1];
     }
-#pragma unroll
-    for (uint32_t j = 0; j < kChainPer; j++) {
-      uint32_t r0 = 0;
-      for (uint32_t n; b < hi && rem >= (n = tile_of(b, s.t, r0)); b++) rem -= n;
-      r[j] = make_uint4(0, 0, 0, 0);
-      if (b < hi) {
-        const u32x4 v = *gp(reinterpret_cast<const u32x4*>(recs + (uint64_t)b * ch.rec_cap + r0 + rem));
-        r[j] = make_uint4(v.x, v.y, v.z, v.w);
-        on |= 1u << j;
-      }
-      rem += stride;
-    }
-    return on;
+    for (uint32_t n; b < hi && rem >= (n = tile_of(b, s.t, r0)); b++) rem -= n;
+    r = make_uint4(0, 0, 0, 0);
+    if (b >= hi) return false;
+    const u32x4 v = *gp(reinterpret_cast<const u32x4*>(recs + (uint64_t)b * ch.rec_cap + r0 + rem));
+    r = make_uint4(v.x, v.y, v.z, v.w);
+    return true;
   };
   Step s = open_step(0, 0);
   uint32_t q0 = 0, done = 0;
   bool give_up = false;
   unsigned long long c0 = a.trace ? (unsigned long long)wall_clock64() : 0ull;
-  uint32_t on = fetch(s, 0, cur);
+  bool on = fetch(s, 0, cur);
   while (s.l < n_lv) {
-    uint4 v[kChainPer];
-#pragma unroll
-    for (uint32_t j = 0; j < kChainPer; j++) v[j] = rec_load(cur[j], (on >> j) & 1);
+    const uint4 v = rec_load(cur, on);
     // the records that follow: of this step, or the next one's first
     const bool end = q0 + batch >= s.n;
     Step sn = s;
@@ -2075,10 +2066,8 @@ __global__ __launch_bounds__(kChainThreads) __attribute__((amdgpu_waves_per_eu(2
       sn = s.t + 1 < s.tiles ? open_step(s.l, s.t + 1) : open_step(s.l + 1, 0);
       qn = 0;
     }
-    const uint32_t on_n = fetch(sn, qn, nxt);
-#pragma unroll
-    for (uint32_t j = 0; j < kChainPer; j++)
-      if ((on >> j) & 1) rec_store(cur[j], v[j]);
+    const bool on_n = fetch(sn, qn, nxt);
+    if (on) rec_store(cur, v);
     if (end) {
       if (s.t == 0) {  // blocks without records, one to a member
         for (uint32_t b = s_lv[s.l] + rank; b < s_lv[s.l + 1]; b += members) {
@@ -2124,8 +2113,7 @@ __global__ __launch_bounds__(kChainThreads) __attribute__((amdgpu_waves_per_eu(2
         c0 = c1;
       }
     }
-#pragma unroll
-    for (uint32_t j = 0; j < kChainPer; j++) cur[j] = nxt[j];
+    cur = nxt;
     on = on_n;
     s = sn;
     q0 = qn;
@@ -2458,7 +2446,6 @@ __global__ __launch_bounds__(1024) void k_bscan(BatchArgs b, uint32_t n_chunks) 
 __device__ __forceinline__ void place_block(const BatchArgs& b, uint32_t j, uint32_t blk, uint32_t f, uint32_t pos,
                                             uint32_t seq) {
   if (j >= b.n_blocks) return;
-  b.pre[j] = pos;
   // the first position of a level: that level's plan start
   const uint32_t lv = ld32(b.arch + kHdr + (uint64_t)kBlk * blk + 16);
   if (b.lstart[lv] == j) b.lvl_dev[lv] = pos;
