@@ -329,7 +329,8 @@ class Archive:
 
     def seek(self, lo: int, hi: int, out=None, ws=None, tuning=None, stream=None, plan: str = "auto"):
         """[lo, hi) as a device tensor.  plan: "host" walks the closure on the
-        host (the workspace capacity passed is the host plan's need), "device"
+        host (the workspace capacity passed is the host plan's need, and below
+        the size that selects the device's planner), "device"
         plans on the device (needs the resident plan), "auto" lets the
         library choose by the workspace's size."""
         torch = self._torch
@@ -357,7 +358,11 @@ class Archive:
                 ws = self.workspace(host_need)
             cap = ws.numel()
             if plan == "host":
+                # below the size that selects device planning (a host plan
+                # never needs that much; at most its records have no room)
                 cap = min(cap, host_need)
+                if self.d_plan is not None:
+                    cap = min(cap, self.seek_device_bytes() - 1)
         _check(lib().ace_seek(self._h, lo, hi, C.c_void_p(out.data_ptr()),
                               C.c_void_p(ws.data_ptr()), cap, self._tuning(tuning),
                               _stream_ptr(stream)))
