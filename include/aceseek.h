@@ -256,7 +256,10 @@ int ace_check(void* d_ws, void* stream);
  * any batch up to the capacity replays the same graph.  The workspace must
  * stay dedicated to the context.  Runs are asynchronous on the stream; a run
  * waits for the previous run of the same context to have read its
- * descriptors.  Errors are read with ace_check(d_ws, stream). */
+ * descriptors.  Errors are read with ace_check(d_ws, stream).
+ * ace_batch_workspace_bytes counts copy records and the whole-archive plan; a
+ * workspace that holds all but these is taken too, and its context runs a
+ * launch per level and plans from the archive's own index. */
 typedef struct ace_batch ace_batch;
 int ace_batch_workspace_bytes(const ace_archive* a, uint32_t max_requests, uint64_t* bytes);
 int ace_batch_create(const ace_archive* a, uint32_t max_requests, void* d_ws, uint64_t ws_cap,

@@ -123,7 +123,8 @@ struct BatchArgs {
   uint64_t* loc;
   const uint8_t* pin;        // per block: 1 = decoded once and kept (its loc stays valid); null: none kept
   const uint32_t* pin_base;  // slots taken by kept blocks; planned blocks go after them (null: none)
-  const PlanEntry* all;      // the whole-archive plan's entries: all blocks by level (static)
+  const PlanEntry* all;      // the whole-archive plan's entries: all blocks by level (static), or null:
+  const uint32_t* order;     // the blocks' ids in that order
   uint32_t* chunk_cnt;       // compaction: per chunk of `all`, needed blocks (then their prefix)
   uint32_t* chunk_seq;       // and their sequences; batch_compact_chunks + 1 entries each
 };

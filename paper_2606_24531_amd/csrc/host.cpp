@@ -1173,10 +1173,13 @@ struct ace_batch {
 namespace {
 struct BatchLayout {
   uint64_t lstart, need, plan, nplan, lvl, loc, lit, lens, offs, slots, desc, pin, pinbase,
-      chunks, all, base, ends, sync, recs, total;
+      chunks, all, order, base, ends, sync, recs, total;
 };
 
-BatchLayout batch_layout(const ace_archive* A, uint32_t cap) {
+// bare: without copy records, and with the block ids by level in the place of
+// the whole-archive plan (the planner then reads the blocks' fields in the
+// archive).
+BatchLayout batch_layout(const ace_archive* A, uint32_t cap, bool bare = false) {
   BatchLayout L;
   uint64_t o = kWsHeader;
   auto take = [&](uint64_t bytes) {
@@ -1198,8 +1201,9 @@ BatchLayout batch_layout(const ace_archive* A, uint32_t cap) {
   L.pin = take(align_up(A->nb, 4));
   L.pinbase = take(4);
   L.chunks = take(8ull * (batch_compact_chunks(A->nb) + 1));
-  L.all = take(sizeof(PlanEntry) * A->nb);
-  layout_records(A, A->rec_dev, L, o);
+  L.all = take(bare ? 0 : sizeof(PlanEntry) * A->nb);
+  L.order = take(bare ? 4ull * A->nb : 0);
+  layout_records(A, bare ? 0 : A->rec_dev, L, o);
   return L;
 }
 
@@ -1356,7 +1360,9 @@ extern "C" int ace_batch_create(const ace_archive* A, uint32_t cap, void* d_ws, 
   if (!A || !d_ws || !out || cap == 0) return fail(ACE_E_ARG, "null argument or zero capacity");
   if (int rc = need_resident(A)) return rc;
   if (!stream) return fail(ACE_E_ARG, "a batch needs a stream of its own: the default stream cannot be captured");
-  const BatchLayout L = batch_layout(A, cap);
+  BatchLayout L = batch_layout(A, cap);
+  const bool bare = ws_cap < L.total;
+  if (bare) L = batch_layout(A, cap, true);
   if (ws_cap < L.total) return fail(ACE_E_NOSPACE, "workspace needs %llu bytes", (unsigned long long)L.total);
   ace_batch* b = new (std::nothrow) ace_batch();
   if (!b) return fail(ACE_E_NOMEM, "out of memory");
@@ -1374,13 +1380,16 @@ extern "C" int ace_batch_create(const ace_archive* A, uint32_t cap, void* d_ws, 
       rc = fail(ACE_E_HIP, "pinned staging or event allocation failed");
       break;
     }
-    // static planning data: all blocks by level with their index fields, and
-    // the level boundaries (a copy of its own: the resident plan may be
-    // attached elsewhere while the context lives)
+    // static planning data: all blocks by level with their index fields (bare:
+    // their ids), and the level boundaries (a copy of its own: the resident
+    // plan may be attached elsewhere while the context lives)
+    std::vector<uint32_t> ids(bare ? A->nb : 0);
+    for (size_t i = 0; i < ids.size(); i++) ids[i] = A->all_plan[i].block;
     if (hipMemcpyAsync(b->ws + L.lstart, A->all_levels.data(), 4ull * (A->depth + 1),
                        hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(b->ws + L.all, A->all_plan.data(), sizeof(PlanEntry) * A->nb, hipMemcpyHostToDevice, s) !=
-            hipSuccess ||
+        (bare ? hipMemcpyAsync(b->ws + L.order, ids.data(), 4 * ids.size(), hipMemcpyHostToDevice, s)
+              : hipMemcpyAsync(b->ws + L.all, A->all_plan.data(), sizeof(PlanEntry) * A->nb, hipMemcpyHostToDevice,
+                               s)) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess) {
       rc = fail(ACE_E_HIP, "upload of the level order failed");
       break;
@@ -1401,7 +1410,8 @@ extern "C" int ace_batch_create(const ace_archive* A, uint32_t cap, void* d_ws, 
     ba.loc = reinterpret_cast<uint64_t*>(b->ws + L.loc);
     ba.pin = b->ws + L.pin;
     ba.pin_base = reinterpret_cast<const uint32_t*>(b->ws + L.pinbase);
-    ba.all = reinterpret_cast<const PlanEntry*>(b->ws + L.all);
+    if (bare) ba.order = reinterpret_cast<const uint32_t*>(b->ws + L.order);
+    else ba.all = reinterpret_cast<const PlanEntry*>(b->ws + L.all);
     ba.chunk_cnt = reinterpret_cast<uint32_t*>(b->ws + L.chunks);
     ba.chunk_seq = ba.chunk_cnt + batch_compact_chunks(A->nb) + 1;
     b->off_plan = L.plan;
@@ -1496,7 +1506,7 @@ extern "C" int ace_batch_create(const ace_archive* A, uint32_t cap, void* d_ws, 
       }
     } else if (e == hipSuccess) {
       e = launch_rans_dev(a, A->nb, per_wave, s);
-      if (e == hipSuccess) e = expand_levels_dev(A, a, L, b->ws, true, waves, s);
+      if (e == hipSuccess) e = expand_levels_dev(A, a, L, b->ws, !bare, waves, s);
     }
     if (e == hipSuccess) e = launch_batch_gather(ba, a, 0, s);
     hipError_t e2 = hipStreamEndCapture(s, &b->graph);

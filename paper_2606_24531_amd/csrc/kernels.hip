@@ -2336,7 +2336,17 @@ __global__ __launch_bounds__(256) void k_bclose(BatchArgs b, uint32_t level) {
   const uint32_t lane = threadIdx.x & 63, wpg = blockDim.x >> 6;
   const uint32_t j0 = b.lstart[level], j1 = b.lstart[level + 1];
   for (uint32_t j = j0 + blockIdx.x * wpg + (threadIdx.x >> 6); j < j1; j += gridDim.x * wpg) {
-    const uint32_t blk = b.all[j].block, dep_off = b.all[j].dep_off, dep_cnt = b.all[j].dep_cnt;
+    uint32_t blk, dep_off, dep_cnt;
+    if (b.all) {
+      blk = b.all[j].block;
+      dep_off = b.all[j].dep_off;
+      dep_cnt = b.all[j].dep_cnt;
+    } else {
+      blk = b.order[j];
+      const uint8_t* be = b.arch + kHdr + (uint64_t)kBlk * blk;
+      dep_off = ld32(be + 20);
+      dep_cnt = ld32(be + 24);
+    }
     if (!b.need[blk]) continue;  // uniform over the wavefront
     const uint32_t* deps = reinterpret_cast<const uint32_t*>(b.arch + kHdr + (uint64_t)kBlk * b.n_blocks) + dep_off;
     for (uint32_t k = lane; k < dep_cnt; k += 64) {
@@ -2363,8 +2373,13 @@ __device__ __forceinline__ void need_fields(const BatchArgs& b, uint32_t j, uint
   f = 0;
   ns = 0;
   if (j >= b.n_blocks) return;
-  blk = b.all[j].block;
-  ns = b.all[j].n_seq;
+  if (b.all) {
+    blk = b.all[j].block;
+    ns = b.all[j].n_seq;
+  } else {
+    blk = b.order[j];
+    ns = ld32(b.arch + kHdr + (uint64_t)kBlk * blk + 12);
+  }
   f = b.need[blk] ? 1u : 0u;
   if (!f) ns = 0;
 }
@@ -2442,6 +2457,23 @@ __global__ __launch_bounds__(1024) void k_bscan(BatchArgs b, uint32_t n_chunks) 
   }
 }
 
+// Block blk's plan entry, read from the archive (seq_base and dst not set):
+// for contexts whose workspace has no room for the whole-archive plan.
+__device__ __forceinline__ PlanEntry archive_entry(const BatchArgs& b, uint32_t blk) {
+  const uint8_t* be = b.arch + kHdr + (uint64_t)kBlk * blk;
+  PlanEntry e{};
+  e.block = blk;
+  e.pay = ld64(be);
+  e.n_seq = ld32(be + 12);
+  e.dep_off = ld32(be + 20);
+  e.dep_cnt = ld32(be + 24);
+  const uint8_t* d = b.arch + e.pay;
+  e.n_lit = ld32(d + 4);
+  for (uint32_t t = 0; t < 3; t++)
+    e.raw[t] = ld8(d + kSDesc * t) == 0 ? e.pay + ld32(d + kSDesc * t + 12) : kCoded;
+  return e;
+}
+
 // Places position j of `all` at plan position pos, token slot seq.
 __device__ __forceinline__ void place_block(const BatchArgs& b, uint32_t j, uint32_t blk, uint32_t f, uint32_t pos,
                                             uint32_t seq) {
@@ -2450,7 +2482,7 @@ __device__ __forceinline__ void place_block(const BatchArgs& b, uint32_t j, uint
   const uint32_t lv = ld32(b.arch + kHdr + (uint64_t)kBlk * blk + 16);
   if (b.lstart[lv] == j) b.lvl_dev[lv] = pos;
   if (!f) return;
-  PlanEntry e = b.all[j];
+  PlanEntry e = b.all ? b.all[j] : archive_entry(b, blk);
   e.seq_base = seq;
   e.dst = (uint64_t)((b.pin_base ? *b.pin_base : 0u) + pos) * b.B;
   b.plan[pos] = e;
