@@ -31,7 +31,10 @@ void operator delete[](void* p, size_t) noexcept { free(p); }
 static std::atomic<int> g_buffers{0};
 static hipError_t counted_malloc(void** p, size_t n) {
   g_buffers++;
-  return hipMalloc(p, n);
+  t_quiet++;  // the stand-in runtime's own allocations
+  const hipError_t r = hipMalloc(p, n);
+  t_quiet--;
+  return r;
 }
 static hipError_t counted_free(void* p) {
   g_buffers--;
