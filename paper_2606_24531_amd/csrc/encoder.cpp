@@ -203,8 +203,13 @@ struct Chains {
 void build_chains(const uint8_t* x, uint64_t n, uint32_t k, Pool& pool, Chains& C) {
   constexpr uint64_t kSegment = 1ull << 28;
   // with fewer threads, a pass each costs less than the sort (8 MiB encoded by
-  // one thread: 0.53 s against 0.87)
+  // two threads 204 ms against 265, by three 175 against 183), but for inputs
+  // whose sorted positions stay in the caches (two threads: 300 KB 6.4 against
+  // 4.2 ms, 1 MiB 20.6 against 19.9, 3 MiB 65 against 84; three: 5.6 against 3.4,
+  // 19.4 against 14.2, 59 against 59); one thread has nothing to share (8 MiB
+  // 0.53 s against 0.87)
   constexpr unsigned kSortThreads = 4;
+  constexpr uint64_t kSortSmall = 1ull << 20;
   const uint32_t hb = hash_bits(n);
   if (n < k) return;
   const uint64_t npos = n - k + 1;
@@ -223,7 +228,7 @@ void build_chains(const uint8_t* x, uint64_t n, uint32_t k, Pool& pool, Chains& 
     }
   };
   BigArray<uint32_t> head(1ull << hb);
-  if (pool.threads() < kSortThreads) {  // each thread links a part of the buckets, over all positions
+  if (pool.threads() < (npos <= kSortSmall ? 2 : kSortThreads)) {  // each thread links a part of the buckets, over all positions
     const uint64_t T = pool.threads(), nbk = 1ull << hb;
     pool.run(T, [&](uint64_t t) {
       const uint32_t lo = (uint32_t)(nbk * t / T), hi = (uint32_t)(nbk * (t + 1) / T);
