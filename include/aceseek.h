@@ -86,9 +86,12 @@ typedef struct {
  *                   blocks in flight)
  *  blocks_per_wg    blocks whose streams one entropy wavefront decodes side
  *                   by side: 1, or 2 when the interleave is at most 32
- *                   (0 = 2 when possible)
- *  lut_variant      entropy table layout in LDS: 0 = 4096-byte slot->symbol
- *                   map plus one (f-1, cum) word per symbol (the only one)
+ *                   (0 = 2 when possible in launches of more than 2,304 blocks,
+ *                   else 1)
+ *  lut_variant      entropy table layout in LDS: 0 (the only value) = by launch:
+ *                   one word per slot for up to 2,304 blocks at one stream per
+ *                   wavefront, else a 4096-byte slot->symbol map plus one
+ *                   (f-1, cum) word per symbol
  *  grid_wgs         workgroups of the persistent expansion (0 = as many as
  *                   the device holds at once; never more than the planned
  *                   blocks)
@@ -251,7 +254,8 @@ int ace_check(void* d_ws, void* stream);
  * uploads the request descriptors (one small host-to-device copy) and
  * replays the graph: device-side planning (targets of every request, their
  * dependency closure, a level-ordered plan), the decode of the union into
- * workspace slots (one entropy launch, one expansion launch per level), and
+ * workspace slots (one entropy launch, then the expansion as ace_tuning's mode
+ * describes), and
  * a gather of every request to its output offset.  Capacity is fixed at creation; counts are read on the device, so
  * any batch up to the capacity replays the same graph.  The workspace must
  * stay dedicated to the context.  Runs are asynchronous on the stream; a run
@@ -299,7 +303,8 @@ int ace_set_timing(int on);
  * decode or seek issued by the calling thread records, per planned block i
  * (plan order = level order), eight u64 values of the device's 100 MHz
  * constant clock at d_trace[8 i ...]: the start and end of the block's match
- * expansion, then start and end of its LIT, LEN and OFF entropy decode (left
+ * expansion (of a recorded block's copies; within one launch of many levels,
+ * of its level's), then start and end of its LIT, LEN and OFF entropy decode (left
  * untouched for streams stored raw).  A decode that plans more blocks than
  * bytes / 64 fails with ACE_E_NOSPACE.  The caller owns the buffer. */
 int ace_set_block_trace(void* d_trace, uint64_t bytes);

@@ -91,8 +91,9 @@ struct ChainArgs {
 
 // Entropy coding of token streams on the device (the encoder's rANS step):
 // stream i has n[i] symbols at sym + sym_off[i]; its coded form (table,
-// W states, words) is written at out + out_off[i] (capacity 544 + 4 W +
-// 2 n[i]), its byte count to out_len[i] (0: the stream stays raw), with
+// W states, words) is written at out + out_off[i] (capacity n[i], as it is
+// written only where it is smaller; 544 + 4 W + 2 n[i] where policy is 1), its
+// byte count to out_len[i] (0: the stream stays raw), with
 // scratch + scr_off[i] (2 n[i] bytes) for the words.  policy: 0 rANS when
 // smaller than raw, 1 always rANS, 2 always raw.
 struct EncArgs {
@@ -130,7 +131,8 @@ struct BatchArgs {
 };
 
 // Kernel launchers (kernels.hip).  All asynchronous on `s`.
-// per_wave: streams one wavefront decodes (0 = 2 when W <= 32, else 1);
+// per_wave: streams one wavefront decodes (0 = 2 when W <= 32 and the launch has
+// more than 2,304 blocks, else 1);
 // waves: wavefronts per block in the expansion (1, 2, 4 or 8; 0 = 4 while
 // the launch's blocks fit on the device at once as four-wavefront
 // workgroups, else 2)

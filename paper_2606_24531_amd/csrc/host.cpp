@@ -231,20 +231,24 @@ static void level_order(const ace_archive* A, const std::vector<uint32_t>& block
 // (launch_copy_level), runs of levels of up to kChainWidth blocks within one
 // launch (launch_chain).  A level's own expansion takes 10 to 28 us whatever its
 // size while its blocks are fewer than the device holds; recording a group takes
-// 15 to 50 us, copying a level 5 to 6 us (12 for 1,000 blocks), and 3.5 us within
-// a chain (which copies 32 blocks of 16 KiB in the time of a launch).  So a group
-// needs kChainRun levels to pay (one more where blocks are larger than
+// 15 to 50 us, copying a level 5 to 6 us (12 for 1,000 blocks), and 3 to 5 us
+// within a chain (which copies 32 blocks of 16 KiB in the time of a launch).  So a
+// group needs kChainRun levels to pay (one more where blocks are larger than
 // kRecBlockSize, whose records take longer: 64 KiB blocks in three levels 207
-// against 189 us), and kRecBlocks blocks at most, as records are memory traffic
-// that a large level does not get back; where the device plans and only the
-// archive's level sizes are known, which a seek's plan seldom reaches,
-// kRecBlocksDev.  Expansion with a launch per level and with groups of up to
-// 1,000, 2,048 and 3,000 blocks: 32 MiB FASTQ (2,048 blocks, of which 960 in the
-// first four levels) 90, 72, 75, 75 us (whole decodes at 1,536 and 2,048: 129 and
-// 136); 9.9 MB of text (988) 88, 62, 62, 62; a range of 1,000 blocks of 2,048 116,
-// 124, 95, 94; 256 MiB mixed 339, 340, 340, 345.  A seek with three levels of 13
-// to 20 blocks among 65 took 500 us with a chain width of 12 and 450 with 32 and
-// 100.
+// against 189 us).
+// kRecBlocks, the blocks of a group at most: records are memory traffic that a
+// large level does not get back.  Whole decodes in four or five levels whose last
+// is left out of the group or is in it: FASTQ 124 and 119 us at 1,700 blocks, 127
+// and 131 at 2,000, 150 and 155 at 2,600; text 189 and 172 at 2,000, 221 and 211 at
+// 2,600; mixed 188 and 145 at 2,600.  So the line lies below FASTQ's turn, where
+// none of them loses; its records take 63 MB.
+// kRecBlocksDev, the same where the device plans: only the archive's level sizes
+// are known, of which a plan reaches a part, so records pay beyond kRecBlocks (a 4
+// KB seek in FASTQ of 2,000 blocks 114 and 112 us, of 2,600 159 and 146, of 3,200
+// 161 and 143; in text of 2,600 227 and 196).  No size was found where they lose;
+// the line holds the records that every such workspace has room for at 84 MB.
+// A seek with three levels of 13 to 20 blocks among 65 took 500 us with a chain
+// width of 12 and 450 with 32 and 100.
 constexpr uint32_t kChainWidth = 32, kChainRun = 3, kRecBlocks = 1536, kRecBlocksDev = 2048, kRecBlockSize = 32768;
 constexpr uint64_t kRecBytes = 128ull << 20;  // records held at a time, at most
 
@@ -1306,7 +1310,8 @@ static int seek_device(const ace_archive* A, uint64_t lo, uint64_t hi, uint8_t* 
     }
     HIP_TRY(launch_persistent(a, t ? t->grid_wgs : 0, s));
   } else {
-    // modes 0, 1 and 3: one entropy launch, then one expansion per level
+    // modes 0, 1 and 3: one entropy launch, then the levels (mode 3: a launch
+    // each; 0 and 1: groups of few blocks recorded)
     HIP_TRY(launch_rans_dev(a, A->nb, per_wave, s));
     if (timed) {
       HIP_TRY(hipEventRecord(T.ent[1], s));

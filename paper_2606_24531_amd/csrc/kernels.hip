@@ -727,10 +727,13 @@ struct ExpandSmem {
   uint32_t scan[32];  // a workgroup's scans: at most four words per wavefront, eight wavefronts
 };
 
-// A workgroup barrier that orders LDS accesses only: global loads and stores
-// still in flight stay in flight (__syncthreads also waits for every one of
-// them).  The expansion's barriers guard its LDS tables; its global reads
-// never touch bytes written earlier in the same tile.
+// A workgroup barrier that orders LDS accesses only.  Neither it nor
+// __syncthreads waits for global loads and stores in flight; __syncthreads
+// orders them as well, between the wavefronts of the workgroup, whose accesses
+// pass their CU's vector cache in turn (what another CU is to read needs
+// wait_stores).  The expansion's barriers guard its LDS tables; where it reads
+// its own output (an earlier tile's, and slow_rounds the pieces' and earlier
+// rounds'), it takes __syncthreads first.
 __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
   __builtin_amdgcn_s_barrier();
@@ -1038,8 +1041,9 @@ __device__ __forceinline__ const uint8_t* slow_ext_addr(const DecodeArgs& a, con
 // the round, always an earlier one.  Those chains are followed in LDS, one
 // hop per step for all of a thread's bytes, each step leaving what it found
 // for the bytes behind it, so a chain of n takes about log2(n) steps.  Then
-// every byte is read from the output (after a barrier that waits for the
-// stores before it) and written, all of a thread's loads in flight at once.
+// every byte is read from the output (after a barrier that orders the reads
+// behind the workgroup's stores) and written, all of a thread's loads in
+// flight at once.
 // Returns the bytes that came from earlier blocks.  The LDS dependency list
 // is overwritten when there is more than one round (it then holds one bit per
 // slow byte: from an earlier block).  Every thread must call it.
@@ -1125,7 +1129,7 @@ __device__ __forceinline__ uint32_t slow_rounds(const DecodeArgs& a, ExpandSmem<
         pend = pend || (e[j] & kFromSlow);
       }
     }
-    __syncthreads();  // every byte read below has been stored; all chains are read
+    __syncthreads();  // the stores of the bytes read below come first; all chains are read
     uint8_t v[kSlowPer];
 #pragma unroll
     for (uint32_t j = 0; j < kSlowPer; j++) {
@@ -1808,13 +1812,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kThrea
 // expanded).  Expansion of a 4 KB seek 74 -> 59 us, of 9.9 MB of text in four
 // levels 88 -> 62, of 32 MiB FASTQ in five 90 -> 75.
 // What bounds a chain's level is a load's and a store's latency and the hand-over,
-// about 3.5 us (a counter at agent scope instead of in the L2, and every wave
-// dropping the vector cache, made it 6.5 us).  One workgroup alone (no
+// 3.1 us in all with three to six blocks a level (601 us for 191 levels) and 5.3
+// with a dozen, where finding a record's block takes longer (a counter at agent
+// scope instead of in the L2, and every wave dropping the vector cache, made it
+// 6.5 us with few blocks).  One workgroup alone (no
 // hand-over) is bounded by its CU's address processing, some 340 cycles per
 // 64 records (scattered 16-byte loads and stores): 8.6 us for a level of three
 // 16 KiB blocks.  A thread's records of the next level are loaded while this
 // one is copied.  Whole decodes, a launch per level before: 12 MiB mixed of 192
-// levels 3.10 -> 0.69 ms, 1 MiB genome of 27 levels 0.51 -> 0.18 ms, 6 MiB
+// levels 3.83 -> 0.70 ms, 1 MiB genome of 27 levels 0.46 -> 0.15 ms, 6 MiB
 // FASTQ 4.05 -> 0.85 ms, 6 MiB text in 64 KiB blocks 6.5 -> 0.82 ms.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kChainThreads = 512;
@@ -2549,11 +2555,14 @@ __global__ void k_fill_u32(uint32_t* p, uint32_t v, uint64_t n) {
 constexpr uint32_t kStrideGridRans = 4096, kStrideGridExpand = 2048;
 
 // Entropy launches of at most this many blocks take wide tables: nine streams
-// per CU on 256 CUs, so the literal streams (the long ones, dispatched first)
-// are all in flight at once.  Measured, wide against narrow: 768 blocks of
-// 64 KiB 103 / 121 us, 988 of 10,000 bytes 40 / 48 us, 2,048 of 16 KiB (W = 32)
-// 63 / 78 us; 16,384 blocks 173 / 87 us (the wide tables leave two wavefronts
-// per SIMD).  Two streams per wavefront asked for by the caller stay narrow.
+// per CU on 256 CUs, so that the literal streams (the long ones, dispatched
+// first) can all be in flight at once.  Measured, wide against narrow: 768
+// blocks of 64 KiB 103 / 121 us, 988 of 10,000 bytes 40 / 48 us; 16 KiB blocks of
+// FASTQ (W = 32, 9 KB streams) 63 / 78 us at 2,048, 86 / 77 at 2,200, 91 / 78 at
+// 2,600; of text 63 / 73 at 2,200, 67 / 73 at 2,600, 79 / 74 at 3,200; of mixed (W =
+// 64) 40 / 41 at 2,600, 62 / 44 at 4,500; 16,384 blocks 173 / 87 us (the wide
+// tables leave two wavefronts per SIMD).  The corpora turn on either side of the
+// line.  Two streams per wavefront asked for by the caller stay narrow.
 constexpr uint32_t kWideBlocks = 2304;
 
 // Entropy launch over plan entries [lo, hi), or (lv_lo >= 0) over the plan
