@@ -287,7 +287,10 @@ void ace_batch_destroy(ace_batch* b);
 
 /* Waits for the stream, then reads and clears the workspace's counter of
  * match bytes that were copied from earlier blocks (the external source
- * bytes of every decode since the last read).  With the archive size and the
+ * bytes of every decode since the last read; sources are followed back within
+ * a tile of the expansion, and a byte of an earlier tile of the same block
+ * counts as the block's own, so that the count of a block of several tiles
+ * depends on the launch shape).  With the archive size and the
  * output size this gives the algorithmic HBM bytes of a decode. */
 int ace_read_counters(void* d_ws, void* stream, uint64_t* ext_src_bytes);
 
