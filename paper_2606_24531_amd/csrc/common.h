@@ -45,6 +45,7 @@ struct DecodeArgs {
   const PlanEntry* plan;
   uint32_t n_plan;
   uint32_t B, W, ow, n_blocks;
+  uint32_t coded;  // whether the archive has rANS-coded streams at all
   uint64_t n_total;
   uint64_t dst_base;
   uint64_t* loc;   // block id -> device address of its decoded bytes

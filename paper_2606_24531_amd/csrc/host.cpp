@@ -65,6 +65,7 @@ struct ace_archive {
   const uint8_t* d_arch = nullptr;
   uint64_t len = 0, n = 0;
   uint32_t B = 0, W = 0, ow = 0, nb = 0, depth = 0;
+  bool coded = false;  // any stream of any block is rANS-coded
   std::vector<BlockInfo> blk;
   std::vector<uint32_t> deps;
   // whole-archive plan: blocks by level, their token slots, level boundaries
@@ -189,6 +190,7 @@ static int validate(const uint8_t* a, uint64_t len, ace_archive* A) {
       if (mode == 1 && (nsym == 0 || clen < 36 + 4 * A->W))
         return fail(ACE_E_CORRUPT, "block %u stream %d: rANS stream too short", b, t);
       bi.raw[t] = mode == 0 ? pay + off : kCoded;
+      A->coded |= mode != 0;
       if (t == 0) bi.n_lit = nsym;
     }
   }
@@ -631,6 +633,7 @@ static int run_launches(const ace_archive* A, const PlanEntry* entries, uint64_t
   a.B = A->B;
   a.b_shift = shift_of(A->B);
   a.W = A->W;
+  a.coded = A->coded;
   a.ow = A->ow;
   a.n_blocks = A->nb;
   a.n_total = A->n;
@@ -1261,6 +1264,7 @@ static int seek_device(const ace_archive* A, uint64_t lo, uint64_t hi, uint8_t* 
   a.B = A->B;
   a.b_shift = shift_of(A->B);
   a.W = A->W;
+  a.coded = A->coded;
   a.ow = A->ow;
   a.n_blocks = A->nb;
   a.n_total = A->n;
@@ -1436,6 +1440,7 @@ extern "C" int ace_batch_create(const ace_archive* A, uint32_t cap, void* d_ws, 
     a.B = A->B;
     a.b_shift = shift_of(A->B);
     a.W = A->W;
+    a.coded = A->coded;
     a.ow = A->ow;
     a.n_blocks = A->nb;
     a.n_total = A->n;

@@ -2568,7 +2568,9 @@ constexpr uint32_t kStrideGridRans = 4096, kStrideGridExpand = 2048;
 // 2,600; of text 63 / 73 at 2,200, 67 / 73 at 2,600, 79 / 74 at 3,200; of mixed (W =
 // 64) 40 / 41 at 2,600, 62 / 44 at 4,500; 16,384 blocks 173 / 87 us (the wide
 // tables leave two wavefronts per SIMD).  The corpora turn on either side of the
-// line.  Two streams per wavefront asked for by the caller stay narrow.
+// line.  Two streams per wavefront asked for by the caller stay narrow, and so
+// do archives without coded streams, whose workgroups only come and go (24 MiB
+// of incompressible data decode in 17.2 us with wide tables, 16.3 with narrow).
 constexpr uint32_t kWideBlocks = 2304;
 
 // Entropy launch over plan entries [lo, hi), or (lv_lo >= 0) over the plan
@@ -2578,7 +2580,7 @@ static hipError_t launch_rans_any(const DecodeArgs& a, uint32_t lo, uint32_t hi,
                                   uint32_t per_wave, hipStream_t s) {
   if (hi <= lo) return hipSuccess;
   const uint32_t n = hi - lo;
-  const bool wide = per_wave != 2 && n <= kWideBlocks;
+  const bool wide = a.coded && per_wave != 2 && n <= kWideBlocks;
   if (per_wave == 0) per_wave = a.W <= 32 && !wide ? 2 : 1;
   const bool two = per_wave == 2 && a.W <= 32;
   uint32_t grid = two ? (n + 1) / 2 : n;
